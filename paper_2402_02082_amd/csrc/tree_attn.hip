@@ -149,10 +149,17 @@ struct Bf16Path {
 struct F32Path {
   static constexpr int kStep = 16;
   typedef float elem_t;
-  struct QFrag { f32x4_t v[8]; };  // d = 32*g + 4*e + (0..3)
+  // Each load instruction takes whole 64-byte pieces of its rows: a K load
+  // 64 contiguous bytes (the four lane groups) of 16 rows, a V load 256 (the
+  // 16 lanes of a group) of 4 rows.  With 32 (K) or 8 (V) consecutive dims
+  // per lane instead, an instruction took 64 separate 16-byte pieces, and
+  // the loads bound the kernel: 13B layer shape (4 x 40 heads, 32 rows,
+  // 1024..4096 keys, 430 MB) 183 -> 112 us, 16 rows 195 -> 109 us, 5 rows
+  // over 2048..8192 keys 584 -> 277 us.
+  struct QFrag { f32x4_t v[8]; };  // d = 16*e + 4*g + (0..3)
   struct KV {
-    f32x4_t k[8];     // key row j0 + c, d = 32*g + 4*e + (0..3)
-    f32x4_t v[4][2];  // key row j0 + 4*g + r, d = 8*c + 4*h + (0..3)
+    f32x4_t k[8];     // key row j0 + c, d = 16*e + 4*g + (0..3)
+    f32x4_t v[4][2];  // key row j0 + 4*g + r, d = 64*h + 4*c + (0..3)
   };
 };
 
@@ -173,7 +180,7 @@ __device__ __forceinline__ void load_q<F32Path>(F32Path::QFrag& f, const float* 
                                                 int g) {
 #pragma unroll
   for (int e = 0; e < 8; ++e)
-    f.v[e] = valid ? *(const f32x4_t*)(qrow + 32 * g + 4 * e) : f32x4_t{0.f, 0.f, 0.f, 0.f};
+    f.v[e] = valid ? *(const f32x4_t*)(qrow + 16 * e + 4 * g) : f32x4_t{0.f, 0.f, 0.f, 0.f};
 }
 
 // K/V rows are fetched with buffer loads.  For each step the descriptor
@@ -239,10 +246,10 @@ __device__ __forceinline__ void load_kv(Bf16Path::KV& f, const char* kslab, cons
   }
 }
 
-// float32 (row = 512 bytes).  K: row c at bytes 128*g + 16*e; V: rows
-// 4*g + r at bytes 32*c + 16*h.
+// float32 (row = 512 bytes).  K: row c at bytes 64*e + 16*g; V: rows
+// 4*g + r at bytes 256*h + 16*c.
 __device__ __forceinline__ LaneOffsets lane_offsets(F32Path, int c, int g) {
-  return LaneOffsets{c * 512 + 128 * g, 0, (4 * g) * 512 + 32 * c, 0};
+  return LaneOffsets{c * 512 + 16 * g, 0, (4 * g) * 512 + 16 * c, 0};
 }
 
 template <int CPOL>
@@ -251,12 +258,12 @@ __device__ __forceinline__ void load_kv(F32Path::KV& f, const char* kslab, const
   const __amdgpu_buffer_rsrc_t rk = step_rsrc(kslab, j0, k_end, 512);
   const __amdgpu_buffer_rsrc_t rv = step_rsrc(vslab, j0, k_end, 512);
 #pragma unroll
-  for (int e = 0; e < 8; ++e) f.k[e] = __builtin_bit_cast(f32x4_t, load16<CPOL>(rk, o.k0 + 16 * e));
+  for (int e = 0; e < 8; ++e) f.k[e] = __builtin_bit_cast(f32x4_t, load16<CPOL>(rk, o.k0 + 64 * e));
 #pragma unroll
   for (int r = 0; r < 4; ++r)
 #pragma unroll
     for (int h = 0; h < 2; ++h)
-      f.v[r][h] = __builtin_bit_cast(f32x4_t, load16<CPOL>(rv, o.v0 + 512 * r + 16 * h));
+      f.v[r][h] = __builtin_bit_cast(f32x4_t, load16<CPOL>(rv, o.v0 + 512 * r + 256 * h));
 }
 
 // Online-softmax state of one 16-query tile for the lane's query column.
@@ -417,18 +424,29 @@ __device__ __forceinline__ void step(const F32Path::KV& f, const F32Path::QFrag 
   }
 }
 
-// Output stores: lane (c, g) owns query column c of each tile and head dims
-// d = 32*g + 8*r + t (t = 0..7) of accumulator element acc[nt][t][r].
-__device__ __forceinline__ void store_row8(uint16_t* dst, const float (&o)[8]) {
+// Output stores: lane (c, g) owns query column c of each tile and, in
+// accumulator elements acc[nt][0..7][r], the head dims
+//   bf16:    d = 32*g + 8*r + (0..7)
+//   float32: d = 16*g + 4*r + (0..3) and 64 + 16*g + 4*r + (0..3)
+// i.e. first_dim + (0..3) and first_dim + kHiDims + (0..3).
+template <class P>
+constexpr int kHiDims = std::is_same<P, Bf16Path>::value ? 4 : 64;
+template <class P>
+__device__ __forceinline__ int first_dim(int g, int r) {
+  return std::is_same<P, Bf16Path>::value ? 32 * g + 8 * r : 16 * g + 4 * r;
+}
+
+// `hi`: distance of the second four dims from the first (bf16 rows: always 4).
+__device__ __forceinline__ void store_row8(uint16_t* dst, const float (&o)[8], int = 4) {
   u32x4_t w;
 #pragma unroll
   for (int e = 0; e < 4; ++e) w[e] = pack_bf16x2(o[2 * e], o[2 * e + 1]);
   *(u32x4_t*)dst = w;
 }
 
-__device__ __forceinline__ void store_row8(float* dst, const float (&o)[8]) {
+__device__ __forceinline__ void store_row8(float* dst, const float (&o)[8], int hi = 4) {
   *(f32x4_t*)dst = f32x4_t{o[0], o[1], o[2], o[3]};
-  *(f32x4_t*)(dst + 4) = f32x4_t{o[4], o[5], o[6], o[7]};
+  *(f32x4_t*)(dst + hi) = f32x4_t{o[4], o[5], o[6], o[7]};
 }
 
 __device__ __forceinline__ void store_2(uint16_t* dst, float a, float b) {
@@ -463,20 +481,21 @@ __device__ __forceinline__ PartialRefs partial_refs(const AttnArgs& a, int b, in
 // `coherent`: device-scope stores for the in-kernel merge; the second-launch
 // merge reads the states after a kernel boundary and takes plain stores.
 template <int CPOL>
-__device__ __forceinline__ void store_partial_row8_p(const PartialRefs& p, int row, int d, const float (&o)[8]) {
+__device__ __forceinline__ void store_partial_row8_p(const PartialRefs& p, int row, int d, const float (&o)[8],
+                                                     int hi) {
   const int off = (row * kD + d) * 4;
   __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, f32x4_t{o[0], o[1], o[2], o[3]}), p.o,
                                          off, 0, CPOL);
   __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, f32x4_t{o[4], o[5], o[6], o[7]}), p.o,
-                                         off + 16, 0, CPOL);
+                                         off + 4 * hi, 0, CPOL);
 }
 
 __device__ __forceinline__ void store_partial_row8(const PartialRefs& p, int row, int d, const float (&o)[8],
-                                                   bool coherent) {
+                                                   int hi, bool coherent) {
   if (coherent)
-    store_partial_row8_p<kDeviceScope>(p, row, d, o);
+    store_partial_row8_p<kDeviceScope>(p, row, d, o, hi);
   else
-    store_partial_row8_p<0>(p, row, d, o);
+    store_partial_row8_p<0>(p, row, d, o, hi);
 }
 
 __device__ __forceinline__ void store_partial_ml(const PartialRefs& p, int row, float m, float l,
@@ -793,7 +812,7 @@ void tree_attn_kernel(AttnArgs args) {
 
   // Merge the waves of each query group through LDS.  Every wave publishes
   // its (max, sum) and its O^T accumulators, then finishes 4 / kWpg of the
-  // four dim blocks r (d = 32 g + 8 r + t) of the group's tiles from all
+  // four dim blocks r (dims: see first_dim) of the group's tiles from all
   // the group's states, so the merge and the stores are shared out instead
   // of left to one wave.  Lane-major float4 layout: conflict-free 16-byte
   // LDS accesses.  States are combined in wave order (results do not depend
@@ -846,14 +865,14 @@ void tree_attn_kernel(AttnArgs args) {
       }
       const float o[8] = {lo4[0] * inv, lo4[1] * inv, lo4[2] * inv, lo4[3] * inv,
                           hi4[0] * inv, hi4[1] * inv, hi4[2] * inv, hi4[3] * inv};
-      const int d = 32 * g + 8 * r;
+      const int d = first_dim<P>(g, r);
       if (half_states) {
         bool fits = true;
 #pragma unroll
         for (int e = 0; e < 8; ++e) fits &= __builtin_fabsf(o[e]) <= kHalfMax;  // false for NaN too
         if (n < N) store_half_row8(half_refs(args, b, h), s * N + n, d, o);
         if (!__all(fits || n >= N)) {  // wave-uniform: rare
-          if (n < N) store_partial_row8(pr, s * N + n, d, o, true);
+          if (n < N) store_partial_row8(pr, s * N + n, d, o, kHiDims<P>, true);
           if (lane == 0) {
             const int bit = 4 * s + r;
             __hip_atomic_fetch_or(args.counters + ((size_t)b * H + h) * kCounterStride + 1 + (bit >> 5),
@@ -862,9 +881,9 @@ void tree_attn_kernel(AttnArgs args) {
         }
       } else if (n < N) {
         if (nsplit == 1)
-          store_row8((elem_t*)args.out + (((size_t)b * N + n) * H + h) * kD + d, o);
+          store_row8((elem_t*)args.out + (((size_t)b * N + n) * H + h) * kD + d, o, kHiDims<P>);
         else
-          store_partial_row8(pr, s * N + n, d, o, args.counters != nullptr);
+          store_partial_row8(pr, s * N + n, d, o, kHiDims<P>, args.counters != nullptr);
       }
     }
     if (nsplit > 1 && n < N && g == 0 && wig == 0) store_partial_ml(pr, s * N + n, M, L, args.counters != nullptr);
