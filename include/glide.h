@@ -288,8 +288,9 @@ int glide_verify_commit(const float* logits, int V, const int32_t* cand_tokens,
  *   a   [M, K] bfloat16, 16-byte aligned;  w_t [N, K] bfloat16, 16-byte
  *       aligned;  out [M, N] of out_dtype (GLIDE_BF16 rounds to nearest
  *       even, GLIDE_F32 keeps the float32 accumulation).
- *   M >= 1 (128 rows per launch, more rows take further launches, each
- *   reading w_t again); 8 <= K <= 2^20 with K % 8 == 0; N >= 1.
+ *   M >= 1 (past 128 rows: 2-D output tiles for GLIDE_BF16, one launch; for
+ *   GLIDE_F32 a launch per 128 rows, each reading w_t again); 8 <= K <= 2^20
+ *   with K % 8 == 0; N >= 1.
  */
 int glide_rows_matmul(const void* a, const void* w_t, void* out, int M, int K, int N,
                       int out_dtype, hipStream_t stream);

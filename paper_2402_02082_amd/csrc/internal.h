@@ -19,11 +19,15 @@ hipError_t launch_argmax_rows(const float* logits, int rows, int V, int32_t* idx
                               hipStream_t stream);
 
 // out[m, n] = sum_k a[m, k] w_t[n, k] (bf16 in, fp32 accumulation); up to
-// kMaxMatmulRows rows per launch, more rows loop.
+// kMaxMatmulRows rows per launch of the few-row kernels.  More rows take
+// launch_tile_matmul's 2-D tiles when the output is bf16, and several
+// launches when it is float32.
 constexpr int kMaxMatmulRows = 128;
 constexpr int kMaxMatmulK = 1 << 20;
 hipError_t launch_rows_matmul(const void* a, const void* w, void* out, int M, int K, int N,
                               bool out_bf16, bool packed, hipStream_t stream);
+hipError_t launch_tile_matmul(const void* a, const void* w, void* out, int M, int K, int N, bool packed,
+                              hipStream_t stream);
 // Bytes of the packed copy of a [N, K] weight matrix: one 1 KB operand block
 // per (16-row tile, 32-wide K step).
 size_t packed_rows_weights_bytes(int K, int N);

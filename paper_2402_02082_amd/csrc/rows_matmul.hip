@@ -384,8 +384,13 @@ hipError_t launch_pack_rows_weights(const void* w_t, void* packed, int K, int N,
 
 hipError_t launch_rows_matmul(const void* a, const void* w, void* out, int M, int K, int N,
                               bool out_bf16, bool packed, hipStream_t stream) {
-  // at most kMaxMatmulRows activation rows per launch; more rows take
-  // further launches, each streaming the weights again
+  // More rows than one launch takes: 2-D output tiles for bf16 outputs (130
+  // rows of K = N = 4096: 30 -> 16 us, 2048 rows 337 -> 66 us).  They add a
+  // row's K steps in one chain, where the few-row kernels add four chains a
+  // quarter as long; next to a bf16 output's rounding that is nothing (both
+  // 1.66e-3 off float64), but a float32 output would lose half a digit, so
+  // it keeps the few-row kernels, each launch streaming the weights again.
+  if (M > kMaxMatmulRows && out_bf16) return launch_tile_matmul(a, w, out, M, K, N, packed, stream);
   for (int m0 = 0; m0 < M; m0 += kMaxMatmulRows) {
     const int rows = min(kMaxMatmulRows, M - m0);
     const uint16_t* ap = (const uint16_t*)a + (size_t)m0 * K;

@@ -136,6 +136,28 @@ def test_rows_matmul_packed(M, K, N, out_dtype):
         assert excess <= 0, excess
 
 
+@pytest.mark.parametrize("M,K,N", [(129, 8, 1), (129, 64, 64), (191, 56, 130), (192, 72, 65), (257, 520, 100),
+                                   (513, 136, 4097), (640, 4104, 4096), (2049, 72, 4100), (2048, 200, 4099)])
+def test_rows_matmul_tiles(M, K, N):
+    """More than 128 rows with a bf16 output: 2-D output tiles of every launch
+    shape (64 x 64, 128 x 64 and 256 x 128), with ragged last tiles, K below,
+    at and past a 64-wide chunk, and N that does and does not allow 8-byte
+    stores; the packed copy gives the same bits."""
+    require_gpu()
+    say("rows_matmul tiles", dict(M=M, K=K, N=N))
+    a = _bf16((M, K), 21 + M).cuda()
+    w_t = _bf16((N, K), 22 + N, 1.0 / np.sqrt(K)).cuda()
+    guard = torch.full((M + 1, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+    got, packed = guard[:M], torch.full_like(guard[:M], float("nan"))
+    glide.glide_rows_matmul(a, w_t, got)
+    glide.glide_rows_matmul_packed(a, glide.pack_rows_weights(w_t), packed)
+    torch.cuda.synchronize()
+    assert torch.equal(got.view(torch.int16), packed.view(torch.int16))
+    assert bool(torch.isnan(guard[M]).all())
+    excess = bf16_ok(to64(got), OX.rows_matmul(to64(a), to64(w_t)))
+    assert excess <= 0, excess
+
+
 def test_pack_layout():
     """Unit l of block (t, j) holds w_t[16t + l % 16][32j + 8 (l / 16) .. + 7],
     zeros past N and K (K = 40, N = 17: both edges)."""
