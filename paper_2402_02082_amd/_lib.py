@@ -1,9 +1,14 @@
-"""ctypes binding of libglide.so: argument marshalling only.
+"""Binding of libglide.so: argument marshalling only.
 
 Every function here checks shapes/dtypes/devices of the torch tensors it is
 given, takes their device pointers and calls the C entry point of the same
 name.  No computation happens in Python and there is no fallback: if the
 library is missing or a call fails, an exception is raised.
+
+The calls of the decoding loop try the native checks first (_native,
+csrc/binding.cpp: the same checks and the same call); where those decline --
+an explicit stream, a tensor subclass, or anything that fails a check -- the
+Python checks below them decide (ctypes), and raise with the reason.
 """
 
 import ctypes
@@ -21,6 +26,7 @@ GLIDE_BF16, GLIDE_F32 = 0, 1
 MAX_NODES, MAX_SPLITS, HEAD_DIM, CAPE_MAX_K = 64, 64, 128, 7
 
 _lib = None
+_native = None
 
 
 class GlideError(RuntimeError):
@@ -89,6 +95,32 @@ def load():
     return lib
 
 
+def _bind():
+    """The native binding, given the library's entry points once."""
+    global _native
+    if _native is None:
+        lib = load()
+        try:
+            from . import _native as native
+        except ImportError as e:
+            raise RuntimeError("the native binding is not built or does not load: run "
+                               "`python -m paper_2402_02082_amd.build`") from e
+        native.bind(tuple(ctypes.cast(f, ctypes.c_void_p).value for f in (
+            lib.glide_tree_attn_workspace, lib.glide_tree_attn, lib.glide_verify_commit,
+            lib.cape_expand_workspace, lib.cape_expand, lib.spec_sample_verify, lib.glide_rows_matmul,
+            lib.glide_block_attn)), _raw_stream, _ws_cache)
+        _native = native
+    return _native
+
+
+def _raw_stream(index):
+    return torch.cuda.current_stream(index).cuda_stream
+
+
+# the same handle without building a Stream object, where torch has it
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", _raw_stream)
+
+
 EXPORTED = ["glide_strerror", "glide_last_hip_error", "glide_tree_attn_workspace",
             "glide_tree_attn", "glide_tree_attn_noalloc_max_workspace", "glide_tree_attn_noalloc",
             "cape_expand_workspace", "cape_expand",
@@ -148,7 +180,7 @@ def _alloc_bytes(nbytes, device, stream=None, zero=False):
 # first call, left zero by every call.
 ATTN_COUNTER_BYTES = 2048 * 128
 
-# Workspaces, kept per (device, stream) so that calls that may run
+# Workspaces, kept per (device index, stream handle) so that calls that may run
 # concurrently on different streams never share partial states.  Each is
 # allocated on its stream (see _alloc_bytes), so a replaced one is only
 # reused after that stream's pending work.
@@ -160,7 +192,8 @@ def attn_workspace(B, N, H, L_cap, max_splits, device, stream=None):
     if need == 0:
         return None
     s = torch.cuda.current_stream(device) if stream is None else stream
-    key = (str(device), s.cuda_stream)
+    index = torch.device(device).index
+    key = (torch.cuda.current_device() if index is None else index, s.cuda_stream)
     ws = _ws_cache.get(key)
     if ws is None or ws.numel() < need:
         ws = _alloc_bytes(need, device, s, zero=True)
@@ -172,6 +205,17 @@ def glide_tree_attn(q, k_cache, v_cache, seq_lens, tree_parents, out, scale=0.0,
                     max_splits=0, workspace=None, stream=None):
     """out[b, n, h] = attention of q[b, n, h] over the prefix (and, with
     tree_parents, the node's ancestor-or-self tree rows).  See include/glide.h."""
+    status = (_native or _bind()).tree_attn(q, k_cache, v_cache, seq_lens, tree_parents, out, scale,
+                                            max_splits, workspace, stream)
+    if status is None:
+        return _glide_tree_attn(q, k_cache, v_cache, seq_lens, tree_parents, out, scale, max_splits,
+                                workspace, stream)
+    _check("glide_tree_attn", status)
+    return out
+
+
+def _glide_tree_attn(q, k_cache, v_cache, seq_lens, tree_parents, out, scale, max_splits, workspace,
+                     stream):
     _dev(q, "q")
     _need(q.dtype in (torch.bfloat16, torch.float32), "q must be bfloat16 or float32")
     for name, t in (("k_cache", k_cache), ("v_cache", v_cache), ("out", out)):
@@ -229,6 +273,16 @@ def glide_tree_attn_noalloc(q, k_cache, v_cache, seq_lens, tree_parents, out, sc
 def cape_expand(draft_probs, k, n_max, tokens_out, parents_out, n_nodes_out, fixed=False,
                 workspace=None, stream=None):
     """CaPE expansion of draft_probs [B, gamma, V] into a parent-indexed tree."""
+    status = (_native or _bind()).cape(draft_probs, k, n_max, tokens_out, parents_out, n_nodes_out,
+                                       fixed, workspace, stream)
+    if status is None:
+        return _cape_expand(draft_probs, k, n_max, tokens_out, parents_out, n_nodes_out, fixed,
+                            workspace, stream)
+    _check("cape_expand", status)
+    return tokens_out, parents_out, n_nodes_out
+
+
+def _cape_expand(draft_probs, k, n_max, tokens_out, parents_out, n_nodes_out, fixed, workspace, stream):
     _dev(draft_probs, "draft_probs", torch.float32)
     B, gamma, V = draft_probs.shape
     for name, t, shape in (("tokens_out", tokens_out, (B, n_max)),
@@ -286,6 +340,19 @@ def glide_verify_commit(logits, cand_tokens, parents, k_caches, v_caches, seq_le
     """Argmax of every tree row, greedy acceptance and the commit of the
     accepted path to every layer's K/V cache (in place); see include/glide.h.
     k_caches, v_caches: sequences of per-layer [B, H, L_cap, D] tensors."""
+    status = (_native or _bind()).verify_commit(logits, cand_tokens, parents, k_caches, v_caches,
+                                                seq_lens, seq_lens_out, target_argmax, accept_len,
+                                                last_node, bonus, path, stream)
+    if status is None:
+        return _glide_verify_commit(logits, cand_tokens, parents, k_caches, v_caches, seq_lens,
+                                    seq_lens_out, target_argmax, accept_len, last_node, bonus, path,
+                                    stream)
+    _check("glide_verify_commit", status)
+    return accept_len
+
+
+def _glide_verify_commit(logits, cand_tokens, parents, k_caches, v_caches, seq_lens, seq_lens_out,
+                         target_argmax, accept_len, last_node, bonus, path, stream):
     _dev(logits, "logits", torch.float32)
     _dev(cand_tokens, "cand_tokens", torch.int32)
     B, N = cand_tokens.shape
@@ -327,6 +394,14 @@ def glide_verify_commit(logits, cand_tokens, parents, k_caches, v_caches, seq_le
 def glide_rows_matmul(a, w_t, out, stream=None):
     """out[m, n] = sum_k a[m, k] * w_t[n, k]; a [M, K], w_t [N, K] bfloat16,
     out [M, N] bfloat16 or float32."""
+    status = (_native or _bind()).rows_matmul(a, w_t, out, stream)
+    if status is None:
+        return _glide_rows_matmul(a, w_t, out, stream)
+    _check("glide_rows_matmul", status)
+    return out
+
+
+def _glide_rows_matmul(a, w_t, out, stream):
     _dev(a, "a", torch.bfloat16)
     _dev(w_t, "w_t", torch.bfloat16)
     _need(a.dim() == 2 and w_t.dim() == 2 and a.shape[1] == w_t.shape[1],
@@ -445,6 +520,17 @@ def glide_cross_block_packed(hidden, wq_packed, k_cache, v_cache, seq_lens, wo_p
 def spec_sample_verify(draft_tokens, draft_probs, target_probs, uniforms, accept_len, next_token,
                        stream=None):
     """Speculative-sampling verification of draft chains; see include/glide.h."""
+    status = (_native or _bind()).spec_sample(draft_tokens, draft_probs, target_probs, uniforms,
+                                              accept_len, next_token, stream)
+    if status is None:
+        return _spec_sample_verify(draft_tokens, draft_probs, target_probs, uniforms, accept_len,
+                                   next_token, stream)
+    _check("spec_sample_verify", status)
+    return accept_len, next_token
+
+
+def _spec_sample_verify(draft_tokens, draft_probs, target_probs, uniforms, accept_len, next_token,
+                        stream):
     _dev(draft_tokens, "draft_tokens", torch.int32)
     B, gamma = draft_tokens.shape
     _dev(draft_probs, "draft_probs", torch.float32)
@@ -473,6 +559,14 @@ def glide_expected_speedup(alpha, gamma, c):
 def glide_block_attn(q, k_cache, v_cache, out, block, scale=0.0, stream=None):
     """Block-masked training cross attention: q [B, T, H, D] over the cache's
     positions [0, block * floor(p / block)); bfloat16.  See include/glide.h."""
+    status = (_native or _bind()).block_attn(q, k_cache, v_cache, out, block, scale, stream)
+    if status is None:
+        return _glide_block_attn(q, k_cache, v_cache, out, block, scale, stream)
+    _check("glide_block_attn", status)
+    return out
+
+
+def _glide_block_attn(q, k_cache, v_cache, out, block, scale, stream):
     for name, t in (("q", q), ("k_cache", k_cache), ("v_cache", v_cache), ("out", out)):
         _dev(t, name, torch.bfloat16)
     B, T, H, D = q.shape

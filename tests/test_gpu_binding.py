@@ -1,0 +1,101 @@
+"""The native checks of the binding (csrc/binding.cpp) against the Python
+checks they stand in front of: plain calls give the same results on either
+path (an explicit stream takes the Python path), and every argument that the
+Python checks refuse is declined natively, so that the reason is raised."""
+
+import pytest
+import torch
+
+import paper_2402_02082_amd as glide
+from paper_2402_02082_amd import _lib
+from tests.gpu_common import require_gpu
+
+pytestmark = pytest.mark.gpu
+
+B, N, H, L, G, V = 2, 6, 3, 40, 4, 1001
+I32, F32, BF = torch.int32, torch.float32, torch.bfloat16
+
+
+def _rand(shape, dtype=BF):
+    return torch.randn(shape, device="cuda").to(dtype)
+
+
+def _ints(shape):
+    return torch.zeros(shape, dtype=I32, device="cuda")
+
+
+def _probs(shape):
+    return torch.softmax(3 * _rand(shape, F32), dim=-1)
+
+
+def _tree():
+    return torch.arange(-1, N - 1, dtype=I32, device="cuda").repeat(B, 1).contiguous()
+
+
+def _calls():
+    """name -> (function, native name, positional arguments, output positions)"""
+    lens = torch.tensor([30, 11], dtype=I32, device="cuda")
+    caches = [[_rand((B, H, L, 128)) for _ in range(2)] for _ in range(2)]
+    attn = [_rand((B, N, H, 128)), *[c[0] for c in caches], lens, _tree(), _rand((B, N, H, 128)), 0.0, 0, None]
+    return {
+        "attn": (glide.glide_tree_attn, "tree_attn", attn, [5]),
+        "cross": (glide.glide_tree_attn, "tree_attn", attn[:4] + [None] + attn[5:7] + [3, None], [5]),
+        "commit": (glide.glide_verify_commit, "verify_commit",
+                   [_rand((B, N + 1, V), F32), _ints((B, N)), _tree(), *caches, lens, _ints((B,)),
+                    _ints((B, N + 1)), _ints((B,)), _ints((B,)), None, _ints((B, N))], [6, 7, 8, 9, 11]),
+        "cape": (glide.cape_expand, "cape", [_probs((B, G, V)), 3, 16, _ints((B, 16)), _ints((B, 16)),
+                                             _ints((B,)), False, None], [3, 4, 5]),
+        "sample": (glide.spec_sample_verify, "spec_sample",
+                   [_ints((B, G)), _probs((B, G, V)), _probs((B, G + 1, V)),
+                    torch.rand((B, G + 1), device="cuda"), _ints((B,)), _ints((B,))], [4, 5]),
+        "rows": (glide.glide_rows_matmul, "rows_matmul", [_rand((5, 64)), _rand((33, 64)), _rand((5, 33), F32)],
+                 [2]),
+        "block": (glide.glide_block_attn, "block_attn",
+                  [_rand((B, L, H, 128)), caches[0][0], caches[1][0], _rand((B, L, H, 128)), 5, 0.0], [3]),
+    }
+
+
+NAMES = ["attn", "cross", "commit", "cape", "sample", "rows", "block"]
+
+
+@pytest.mark.parametrize("name", NAMES)
+def test_native_equals_python_path(name):
+    require_gpu()
+    torch.manual_seed(3)
+    fn, native, args, outs = _calls()[name]
+    fn(*args)  # workspaces exist from here on
+    assert getattr(_lib._bind(), native)(*args, None) == 0
+    torch.cuda.synchronize()
+    got = [args[i].clone() for i in outs]
+    for i in outs:
+        args[i].fill_(77)
+    fn(*args, stream=torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    for g, i in zip(got, outs):
+        assert torch.equal(g, args[i])
+
+
+@pytest.mark.parametrize("name", NAMES)
+def test_native_declines_what_python_refuses(name):
+    require_gpu()
+    fn, native, args, _ = _calls()[name]
+    nat = getattr(_lib._bind(), native)
+
+    def refused(bad):
+        assert nat(*bad, None) is None
+        with pytest.raises((ValueError, TypeError, AttributeError)):
+            fn(*bad)
+
+    for i, a in enumerate(args):
+        if isinstance(a, torch.Tensor):
+            bad = [a.cpu(), a.to(torch.float16), a[1:].contiguous(), a.unsqueeze(0).contiguous(),
+                   torch.stack([a, a], dim=-1)[..., 0], a.tolist()]
+        elif isinstance(a, list):
+            bad = [a[:1], a[:1] + [a[1].cpu()], a[:1] + [a[1][:, :, :-1].contiguous()], a[:1] + [a[1].to(F32)],
+                   a[:1] + [torch.stack([a[1], a[1]], dim=-1)[..., 0]]]
+        else:
+            continue
+        for x in bad:
+            if name == "attn" and i == 4 or not (isinstance(x, torch.Tensor) and x.shape == a.shape
+                                                 and x.dtype == a.dtype and x.is_cuda and x.is_contiguous()):
+                refused(args[:i] + [x] + args[i + 1:])
