@@ -5,7 +5,8 @@
 //
 // Two kernels:
 //   cape_top8_part  one workgroup per 4096-token part of a draft row: the 8
-//                   best (prob desc, id asc) tokens of the part;
+//                   best (prob desc, id asc) tokens of the part, ranked among
+//                   the few that pass a threshold;
 //   cape_assemble   one workgroup per sequence: merges the parts into the
 //                   row's top 8 -- the proposal token and the largest possible
 //                   expansion set (S(p) <= 7) -- then applies S(p), the budget
@@ -96,73 +97,138 @@ constexpr int kPart = kThreads * 16;
 
 __device__ __forceinline__ int parts_per_row(int V) { return (V + kPart - 1) / kPart; }
 
-// Top-8 keys of one 4096-element part of one draft row.  Every thread
-// requests its 16 elements at once and keeps its own top 8; the lists are
-// merged with bitonic top-8 merges, across lanes by shuffles and across the
-// four waves through LDS.
+// Max over the 16 lanes of a DPP row, in every lane of the row: swaps of
+// neighbours, pairs, quads (half mirror) and halves (mirror).
+__device__ __forceinline__ float row16_max(float v) {
+  auto step = [&](float o) { v = fmaxf(v, o); };
+  step(__uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(v), 0xB1, 0xF, 0xF, true)));
+  step(__uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(v), 0x4E, 0xF, 0xF, true)));
+  step(__uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(v), 0x141, 0xF, 0xF, true)));
+  step(__uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(v), 0x140, 0xF, 0xF, true)));
+  return v;
+}
+
+constexpr int kWaves = kThreads / 64;
+constexpr int kPerWave = 64;  // candidates a wave can hold
+
+// Top-8 keys of one 4096-element part of one draft row.
+//
+// Bound: latency (one round of loads, then short dependent steps).  Keeping a
+// sorted top 8 per thread (16 insertions of up to seven 64-bit exchanges) and
+// merging the lists across lanes and waves took 9.8 us for 64 rows of 32000,
+// this takes 5.8 (5 rows: 7.5, now 4.6): a threshold leaves only a few candidates: every thread requests its
+// 16 values at once, the maxima of 16 thread groups are paired, and the
+// smallest of the eight pair maxima is passed by at least eight values and,
+// on values in random order, by about 22.  Those are ranked by counting.
+// Parts with more candidates in a wave than it can hold (many values equal to
+// the threshold, such as zeros) take the sorted lists.
 __global__ __launch_bounds__(kThreads) void cape_top8_part(const float* __restrict__ probs, int V,
                                                            uint64_t* __restrict__ top_out) {
   const int part = blockIdx.x, row = blockIdx.y, tid = threadIdx.x;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int P = gridDim.x;
   const float* p = probs + (size_t)row * V;
-  const int base = part * kPart;
+  const int base = part * kPart, left = min(kPart, V - base);
+  uint64_t* out = top_out + ((size_t)row * P + part) * kTopK;
+  __shared__ __attribute__((aligned(16))) float group_max[16];
+  __shared__ uint64_t cand[kWaves][kPerWave];
+  __shared__ int cand_n[kWaves];
+
+  // x[j]: the part's element index_of(j); elements past the row are -inf here
+  // and never candidates
+  const bool vec = (V & 3) == 0 && (((uintptr_t)p) & 15) == 0;
+  float x[16];
+  if (vec) {
+    const float4* p4 = (const float4*)(p + base);
+    float4 x4[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int i = tid + kThreads * u;
+      x4[u] = 4 * i < left ? p4[i] : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      x[4 * u] = x4[u].x;
+      x[4 * u + 1] = x4[u].y;
+      x[4 * u + 2] = x4[u].z;
+      x[4 * u + 3] = x4[u].w;
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+      const int i = tid + kThreads * j;
+      x[j] = i < left ? p[base + i] : -INFINITY;
+    }
+  }
+  auto index_of = [&](int j) { return vec ? 4 * (tid + kThreads * (j >> 2)) + (j & 3) : tid + kThreads * j; };
+
+  float mx = x[0];
+#pragma unroll
+  for (int j = 1; j < 16; ++j) mx = fmaxf(mx, x[j]);
+  mx = row16_max(mx);
+  if ((lane & 15) == 0) group_max[tid >> 4] = mx;
+  __syncthreads();
+  float t = INFINITY;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) t = fminf(t, fmaxf(group_max[i], group_max[i + 8]));
+
+  int n = 0;
+#pragma unroll
+  for (int j = 0; j < 16; ++j) {
+    const bool hit = x[j] >= t && index_of(j) < left;
+    const uint64_t hits = __ballot(hit);
+    if (hits) {
+      const int slot = n + __popcll(hits & ((1ull << lane) - 1ull));
+      if (hit && slot < kPerWave) cand[wave][slot] = rank_key(x[j], base + index_of(j));
+      n += __popcll(hits);
+    }
+  }
+  if (lane == 0) cand_n[wave] = n;
+  __syncthreads();
+  int cn[kWaves], total = 0;
+  bool over = false;
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) {
+    cn[w] = __builtin_amdgcn_readfirstlane(cand_n[w]);
+    total += cn[w];
+    over |= cn[w] > kPerWave;
+  }
+  if (!over) {
+    // each wave ranks its own candidates against all (keys are distinct)
+    const uint64_t mine = lane < n ? cand[wave][lane] : 0;
+    int rank = 0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+#pragma unroll 4
+      for (int o = 0; o < cn[w]; ++o) rank += cand[w][o] > mine;
+    }
+    if (lane < n && rank < kTopK) out[rank] = mine;
+    if (tid >= total && tid < kTopK) out[tid] = 0;  // a part of fewer than eight elements
+    return;
+  }
+
   uint64_t top[kTopK];
 #pragma unroll
   for (int j = 0; j < kTopK; ++j) top[j] = 0;  // below every real key
-
-  if ((V & 3) == 0 && (((uintptr_t)p) & 15) == 0) {
-    const float4* p4 = (const float4*)(p + base);
-    const int n4 = min(kPart, V - base) / 4;
-    float4 x[4];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int i = tid + kThreads * u;
-      x[u] = i < n4 ? p4[i] : make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int i = tid + kThreads * u;
-      if (i < n4) {
-        const int id = base + 4 * i;
-        insert_key(top, rank_key(x[u].x, id));
-        insert_key(top, rank_key(x[u].y, id + 1));
-        insert_key(top, rank_key(x[u].z, id + 2));
-        insert_key(top, rank_key(x[u].w, id + 3));
-      }
-    }
-  } else {
-    float x[16];
-#pragma unroll
-    for (int u = 0; u < 16; ++u) {
-      const int i = base + tid + kThreads * u;
-      x[u] = i < V ? p[i] : 0.f;
-    }
-#pragma unroll
-    for (int u = 0; u < 16; ++u) {
-      const int i = base + tid + kThreads * u;
-      if (i < V) insert_key(top, rank_key(x[u], i));
-    }
-  }
-
+  for (int j = 0; j < 16; ++j)
+    if (index_of(j) < left) insert_key(top, rank_key(x[j], base + index_of(j)));
   // Merge the 64 lists of each wave with shuffles, then the 4 wave lists.
   wave_merge_top8(top, 64);
-  __shared__ uint64_t lists[kThreads / 64][kTopK];
-  const int lane = tid & 63, wave = tid >> 6;
+  __syncthreads();  // every wave has read cand
   if (lane == 0) {
 #pragma unroll
-    for (int j = 0; j < kTopK; ++j) lists[wave][j] = top[j];
+    for (int j = 0; j < kTopK; ++j) cand[wave][j] = top[j];
   }
   __syncthreads();
   if (wave != 0) return;
 #pragma unroll
-  for (int j = 0; j < kTopK; ++j) top[j] = lane < kThreads / 64 ? lists[lane][j] : 0;
-  wave_merge_top8(top, kThreads / 64);
+  for (int j = 0; j < kTopK; ++j) top[j] = lane < kWaves ? cand[lane & (kWaves - 1)][j] : 0;
+  wave_merge_top8(top, kWaves);
   if (lane == 0) {
 #pragma unroll
-    for (int j = 0; j < kTopK; ++j) lists[0][j] = top[j];
+    for (int j = 0; j < kTopK; ++j) out[j] = top[j];
   }
-  __builtin_amdgcn_wave_barrier();
-  if (tid < kTopK) top_out[((size_t)row * P + part) * kTopK + tid] = lists[0][tid];
 }
 
 // S(p): 7, 5, 3, 1 on (0, 0.3], (0.3, 0.6], (0.6, 0.8], (0.8, 1].
@@ -175,10 +241,14 @@ __device__ __forceinline__ int expansion_size(float p) {
 
 // One workgroup per sequence.  First each wave merges the per-part top-8
 // lists of its positions into one top-8 list per position (bitonic merges
-// across lanes).  Then wave 0 assembles the tree: candidate c enumerates
-// (position i, rank r) in linearisation order, and its confidence key is the
-// top-8 key itself.
-constexpr int kAsmThreads = 256;
+// across lanes); eight waves, so that proposals of up to eight tokens load
+// every list in one round.  Then wave 0 assembles the tree: candidate c
+// enumerates (position i, rank r) in linearisation order, and its confidence
+// key is the top-8 key itself.  Sizes, offsets and (up to 64 candidates) the
+// budget ranks pass between lanes in registers: reading them from LDS inside
+// the counting loops cost a dependent LDS round trip per candidate (16-node
+// tree of 5 tokens 6.1 -> 5.1 us, eight trees of 8 tokens 6.6 -> 5.9 us).
+constexpr int kAsmThreads = 512;
 
 __global__ __launch_bounds__(kAsmThreads) void cape_assemble(const uint64_t* __restrict__ part_top,
                                                              int gamma, int V, int k, int fixed,
@@ -214,56 +284,78 @@ __global__ __launch_bounds__(kAsmThreads) void cape_assemble(const uint64_t* __r
   __syncthreads();
   if (wave != 0) return;
 
-  __shared__ int sizes[kMaxNodes];
-  __shared__ int base[kMaxNodes + 1];
   __shared__ uint64_t cand_key[kMaxNodes * 7];
   __shared__ int cand_pos[kMaxNodes * 7];
 
+  int size = 0;
   if (lane < gamma) {
     const uint64_t k0 = top[lane][0];
-    int K;
     if (fixed) {
-      K = k;
+      size = k;
     } else {
-      K = expansion_size(from_ordered_bits((uint32_t)(k0 >> 32)));
-      if (k > 0) K = min(K, k);
+      size = expansion_size(from_ordered_bits((uint32_t)(k0 >> 32)));
+      if (k > 0) size = min(size, k);
     }
-    sizes[lane] = min(K, V - 1);
+    size = min(size, V - 1);
     tokens[(size_t)b * n_max + lane] = key_id(k0);
     parents[(size_t)b * n_max + lane] = lane - 1;
   }
-  __builtin_amdgcn_wave_barrier();
-  if (lane == 0) {
-    int acc = 0;
+  int Ctot = 0;
+  for (int i = 0; i < gamma; ++i) Ctot += __builtin_amdgcn_readlane(size, i);
+  uint64_t my_key = 0;  // the lane's candidate of the first 64
+  int my_pos = 0;
+  for (int cb = 0; cb < Ctot; cb += 64) {
+    // position of candidate cb + lane: the number of positions that end at
+    // or before it
+    const int cidx = cb + lane;
+    int pos = 0, start = 0, end = 0;
     for (int i = 0; i < gamma; ++i) {
-      base[i] = acc;
-      acc += sizes[i];
+      end += __builtin_amdgcn_readlane(size, i);
+      if (cidx >= end) {
+        pos = i + 1;
+        start = end;
+      }
     }
-    base[gamma] = acc;
-  }
-  __builtin_amdgcn_wave_barrier();
-  const int Ctot = base[gamma];
-  for (int cidx = lane; cidx < Ctot; cidx += 64) {
-    int i = 0;
-    while (base[i + 1] <= cidx) ++i;
-    const int r = cidx - base[i] + 1;
-    cand_key[cidx] = top[i][r];
-    cand_pos[cidx] = i;
+    const uint64_t key = cidx < Ctot ? top[pos][cidx - start + 1] : 0;
+    if (cb == 0) {
+      my_key = key;
+      my_pos = pos;
+    }
+    if (cidx < Ctot) {
+      cand_key[cidx] = key;
+      cand_pos[cidx] = pos;
+    }
   }
   __builtin_amdgcn_wave_barrier();
 
   const int budget = n_max - gamma;
   int written = 0;  // kept candidates in earlier chunks
+  // Rank in (prob desc, position asc, rank asc): probability is the high half
+  // of the key; cidx order is (position, rank) order.
+  int ahead64 = 0;
+  if (Ctot > budget && Ctot <= 64) {
+    const uint32_t pc = (uint32_t)(my_key >> 32);
+    for (int o = 0; o < Ctot; ++o) {
+      const uint32_t po = __builtin_amdgcn_readlane(pc, o);
+      ahead64 += (po > pc) || (po == pc && o < lane);
+    }
+  }
   for (int cb = 0; cb < Ctot; cb += 64) {
     const int cidx = cb + lane;
     bool kept = false;
+    uint64_t key = my_key;
+    int pos = my_pos;
     if (cidx < Ctot) {
+      if (Ctot > 64) {
+        key = cand_key[cidx];
+        pos = cand_pos[cidx];
+      }
       if (Ctot <= budget) {
         kept = true;
+      } else if (Ctot <= 64) {
+        kept = ahead64 < budget;
       } else {
-        // Rank in (prob desc, position asc, rank asc): probability is the
-        // high half of the key; cidx order is (position, rank) order.
-        const uint32_t pc = (uint32_t)(cand_key[cidx] >> 32);
+        const uint32_t pc = (uint32_t)(key >> 32);
         int ahead = 0;
         for (int o = 0; o < Ctot; ++o) {
           const uint32_t po = (uint32_t)(cand_key[o] >> 32);
@@ -275,8 +367,8 @@ __global__ __launch_bounds__(kAsmThreads) void cape_assemble(const uint64_t* __r
     const uint64_t mask = __ballot(kept);
     if (kept) {
       const int slot = gamma + written + __popcll(mask & ((1ull << lane) - 1ull));
-      tokens[(size_t)b * n_max + slot] = key_id(cand_key[cidx]);
-      parents[(size_t)b * n_max + slot] = cand_pos[cidx] - 1;
+      tokens[(size_t)b * n_max + slot] = key_id(key);
+      parents[(size_t)b * n_max + slot] = pos - 1;
     }
     written += __popcll(mask);
   }

@@ -172,3 +172,39 @@ def test_tree_verify_planted_cape():
     assert np.array_equal(acc, depth)
     want = OV.tree_verify(ta, tokens, parents)
     assert np.array_equal(last, want[1]) and np.array_equal(bonus, want[2])
+
+
+@pytest.mark.parametrize("V", [4095, 4096, 4097, 4100, 4396, 8193, 32000, 40000])
+@pytest.mark.parametrize("rows", ["normal", "filtered", "constant", "rising", "falling", "steps"])
+def test_cape_candidate_threshold(V, rows):
+    """Rows on which a part's candidate threshold passes few values, all of
+    them, or values tied with it: filtered rows (5 tokens kept, zeros), equal
+    values, sorted rows, and rows of a few distinct values; parts of 1, 4,
+    300 and 4096 elements, aligned rows and not."""
+    require_gpu()
+    rng = np.random.default_rng(V)
+    B, gamma, n_max = 2, 3, 24
+    if rows == "constant":
+        probs = np.full((B, gamma, V), 1.0 / V, dtype=np.float32)
+    elif rows == "steps":
+        probs = rng.integers(0, 4, size=(B, gamma, V)).astype(np.float32) / 4
+    else:
+        probs = rng.dirichlet(np.full(V, 0.3), size=(B, gamma)).astype(np.float32)
+        if rows == "filtered":
+            kept = np.argpartition(probs, -5, axis=-1)[..., -5:]
+            out = np.zeros_like(probs)
+            np.put_along_axis(out, kept, np.take_along_axis(probs, kept, -1), -1)
+            probs = out
+        elif rows != "normal":
+            probs.sort(axis=-1)
+            probs = np.ascontiguousarray(probs[..., ::-1]) if rows == "falling" else probs
+    dev = torch.device("cuda")
+    tok = torch.full((B, n_max), -9, dtype=torch.int32, device=dev)
+    par, nn = torch.full_like(tok, -9), torch.full((B,), -9, dtype=torch.int32, device=dev)
+    say("cape", dict(V=V, rows=rows))
+    glide.cape_expand(torch.from_numpy(probs).to(dev), 0, n_max, tok, par, nn)
+    torch.cuda.synchronize()
+    w_tok, w_par, w_n = OC.cape_expand(probs, 0, n_max)
+    assert np.array_equal(tok.cpu().numpy(), w_tok)
+    assert np.array_equal(par.cpu().numpy(), w_par)
+    assert np.array_equal(nn.cpu().numpy(), w_n)
