@@ -9,9 +9,15 @@
 // rejection picks the target row after the last token.  The token is drawn by
 // inverse CDF over fixed-point weights floor(p * 2^32): integer sums do not
 // depend on the order of summation, so the draw is a function of the inputs
-// alone (each thread sums a contiguous chunk, a block-wide exclusive scan of
-// the chunk sums locates the chunk that holds floor(u * W), and its thread
-// walks it).
+// alone.  Each wave owns a contiguous region of the row and reads it in tiles
+// of 256 tokens, four consecutive tokens a lane; the waves' sums tell which
+// region holds floor(u * W), and that wave scans its tiles for the token.
+//
+// Bound: latency -- the dependent reads of the tokens, their probabilities
+// and the row, then the sums.  With a contiguous run of tokens per thread a
+// row load touched 64 cache lines for 1 KB, and every weight went through
+// float64: 13.0 us for 16 sequences of V = 32000.  A tile load is 1 KB
+// contiguous, and a probability below 1 converts exactly in float32: 8.3 us.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -33,162 +39,117 @@ __device__ __forceinline__ uint64_t shfl_up_u64(uint64_t v, int d) {
   return ((uint64_t)hi << 32) | lo;
 }
 
-// Weight of token v in the chosen row: the residual (mode 0) or the target
-// row itself (mode 1).
-__device__ __forceinline__ uint64_t row_weight(const float* pt, const float* pd, int v, int mode) {
-  if (mode == 1) return fixed_weight(pt[v]);
-  const float r = pt[v] - pd[v];
-  return fixed_weight(r > 0.f ? r : 0.f);
+__device__ __forceinline__ uint64_t shfl_xor_u64(uint64_t v, int m) {
+  const uint32_t lo = __shfl_xor((uint32_t)v, m), hi = __shfl_xor((uint32_t)(v >> 32), m);
+  return ((uint64_t)hi << 32) | lo;
 }
 
-// Exclusive block-wide scan of one uint64 per thread; also returns the total.
-__device__ uint64_t block_exclusive_scan(uint64_t x, uint64_t* total) {
-  __shared__ uint64_t wave_sum[kWaves];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  uint64_t incl = x;
+__device__ __forceinline__ uint64_t readlane_u64(uint64_t v, int lane) {
+  const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)v, lane), hi = __builtin_amdgcn_readlane((uint32_t)(v >> 32), lane);
+  return ((uint64_t)hi << 32) | lo;
+}
+
+constexpr int kTile = 256;  // tokens a wave reads at once
+constexpr int kTiles = 8;   // tiles held in registers (V <= 32768: a wave's whole region)
+constexpr int kGroup = kTile * kTiles;
+
+// Values of tokens v0 + 256 u + 4 lane .. + 3 of the chosen row (0 at and
+// past v1): the target's (mode 1) or the residual max(0, target - draft).
+__device__ __forceinline__ void load_group(float (&p)[kTiles][4], const float* pt, const float* pd, int v0, int v1,
+                                           int mode, bool vec, int lane) {
+  float d[kTiles][4];
 #pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const uint64_t y = shfl_up_u64(incl, d);
-    if (lane >= d) incl += y;
-  }
-  if (lane == 63) wave_sum[wave] = incl;
-  __syncthreads();
-  uint64_t before = 0, all = 0;
-  for (int w = 0; w < kWaves; ++w) {
-    const uint64_t s = wave_sum[w];
-    if (w < wave) before += s;
-    all += s;
-  }
-  __syncthreads();  // wave_sum is reused by the next call
-  *total = all;
-  return before + incl - x;
-}
-
-// Up to kHeld tokens per thread (V <= 4 * kThreads * 8 = 32768): the pass
-// that sums a thread's chunk also parks the chosen row's per-token values in
-// LDS (element-major, so a wave's stores are conflict-free), and the owner of
-// the drawn chunk searches them there instead of reading the rows again.
-constexpr int kHeld = 32;
-
-__device__ uint64_t held_weight(float* held, const float* pt, const float* pd, int v0, int v1, int mode,
-                                bool vec) {
-  const int tid = threadIdx.x;
-  uint64_t sum = 0;
-  if (vec) {
-#pragma unroll 2
-    for (int i = 0; i < kHeld; i += 4) {
-      const int v = v0 + i;
-      float4 a = make_float4(0.f, 0.f, 0.f, 0.f), d = a;
+  for (int u = 0; u < kTiles; ++u) {
+    const int v = v0 + kTile * u + 4 * lane;
+    if (vec) {
+      float4 a = make_float4(0.f, 0.f, 0.f, 0.f), b = a;
       if (v < v1) {
         a = *(const float4*)(pt + v);
-        if (mode == 0) d = *(const float4*)(pd + v);
+        if (mode == 0) b = *(const float4*)(pd + v);
       }
-      const float av[4] = {a.x, a.y, a.z, a.w}, dv[4] = {d.x, d.y, d.z, d.w};
+      p[u][0] = a.x, p[u][1] = a.y, p[u][2] = a.z, p[u][3] = a.w;
+      d[u][0] = b.x, d[u][1] = b.y, d[u][2] = b.z, d[u][3] = b.w;
+    } else {
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        float p = av[e];
-        if (mode == 0) {
-          const float r = av[e] - dv[e];
-          p = r > 0.f ? r : 0.f;
-        }
-        held[(i + e) * kThreads + tid] = p;
-        sum += fixed_weight(p);
+        p[u][e] = v + e < v1 ? pt[v + e] : 0.f;
+        d[u][e] = mode == 0 && v + e < v1 ? pd[v + e] : 0.f;
       }
     }
+  }
+#pragma unroll
+  for (int u = 0; u < kTiles; ++u)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) p[u][e] = fmaxf(p[u][e] - d[u][e], 0.f);
+}
+
+// s[u]: sum of the lane's four weights of tile u.  p * 2^32 is exact in
+// float32, and below 2^32 its integer part fits 32 bits; only values of 1 and
+// more take the float64 conversion.
+__device__ __forceinline__ void group_weights(const float (&p)[kTiles][4], uint64_t (&s)[kTiles]) {
+  float top = 0.f;
+#pragma unroll
+  for (int u = 0; u < kTiles; ++u)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) top = fmaxf(top, p[u][e]);
+  if (__any(top >= 1.f)) {
+#pragma unroll
+    for (int u = 0; u < kTiles; ++u)
+      s[u] = (fixed_weight(p[u][0]) + fixed_weight(p[u][1])) + (fixed_weight(p[u][2]) + fixed_weight(p[u][3]));
   } else {
-    for (int i = 0; i < kHeld; ++i) {
-      const int v = v0 + i;
-      float p = 0.f;
-      if (v < v1) {
-        p = pt[v];
-        if (mode == 0) {
-          const float r = p - pd[v];
-          p = r > 0.f ? r : 0.f;
+#pragma unroll
+    for (int u = 0; u < kTiles; ++u) {
+      s[u] = 0;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) s[u] += (uint32_t)(p[u][e] * 4294967296.f);
+    }
+  }
+}
+
+// Called by a whole wave: the token of the group starting at v0 whose running
+// weight first exceeds `left` (written by its lane), or `left` less the
+// group's weight.  Returns whether the token was in the group.
+__device__ bool find_in_group(const float (&p)[kTiles][4], int v0, uint64_t& left, int lane, int32_t* token) {
+  uint64_t s[kTiles], own[kTiles];
+  group_weights(p, own);
+#pragma unroll
+  for (int u = 0; u < kTiles; ++u) s[u] = own[u];
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+#pragma unroll
+    for (int u = 0; u < kTiles; ++u) {
+      const uint64_t y = shfl_up_u64(s[u], d);
+      if (lane >= d) s[u] += y;
+    }
+  }
+  bool found = false;
+#pragma unroll
+  for (int u = 0; u < kTiles; ++u) {
+    if (!found) {
+      const uint64_t tile = readlane_u64(s[u], 63);
+      if (left < tile) {
+        found = true;
+        uint64_t run = s[u] - own[u];
+        if (run <= left && left < s[u]) {
+          int at = 3;
+#pragma unroll
+          for (int e = 0; e < 3; ++e) {
+            run += fixed_weight(p[u][e]);
+            if (run > left) {
+              at = e;
+              break;
+            }
+          }
+          *token = v0 + kTile * u + 4 * lane + at;
         }
-      }
-      held[i * kThreads + tid] = p;
-      sum += fixed_weight(p);
-    }
-  }
-  return sum;
-}
-
-__device__ int held_find(const float* held, int v0, int v1, uint64_t run, uint64_t t) {
-  const int tid = threadIdx.x;
-  int found = v1 - 1;
-  bool done = false;
-  for (int i = 0; i < kHeld && v0 + i < v1; ++i) {
-    run += fixed_weight(held[i * kThreads + tid]);
-    if (!done && run > t) {
-      found = v0 + i;
-      done = true;
-    }
-  }
-  return found;
-}
-
-// Sum of the weights of tokens [v0, v1).
-__device__ uint64_t chunk_weight(const float* pt, const float* pd, int v0, int v1, int mode, bool vec) {
-  uint64_t sum = 0;
-  if (vec) {
-#pragma unroll 8
-    for (int v = v0; v < v1; v += 4) {
-      const float4 a = *(const float4*)(pt + v);
-      const float4 d = mode == 1 ? a : *(const float4*)(pd + v);
-      if (mode == 1) {
-        sum += fixed_weight(a.x) + fixed_weight(a.y) + fixed_weight(a.z) + fixed_weight(a.w);
       } else {
-        const float r0 = a.x - d.x, r1 = a.y - d.y, r2 = a.z - d.z, r3 = a.w - d.w;
-        sum += fixed_weight(r0 > 0.f ? r0 : 0.f) + fixed_weight(r1 > 0.f ? r1 : 0.f) +
-               fixed_weight(r2 > 0.f ? r2 : 0.f) + fixed_weight(r3 > 0.f ? r3 : 0.f);
-      }
-    }
-  } else {
-    for (int v = v0; v < v1; ++v) sum += row_weight(pt, pd, v, mode);
-  }
-  return sum;
-}
-
-// The first token of [v0, v1) whose running weight (from `run`) exceeds t;
-// the running sum is taken without an early exit so the loads go out
-// together.
-__device__ int chunk_find(const float* pt, const float* pd, int v0, int v1, int mode, bool vec,
-                          uint64_t run, uint64_t t) {
-  int found = v1 - 1;
-  bool done = false;
-  if (vec) {
-#pragma unroll 8
-    for (int v = v0; v < v1; v += 4) {
-      const float4 a = *(const float4*)(pt + v);
-      const float4 d = mode == 1 ? a : *(const float4*)(pd + v);
-      const float av[4] = {a.x, a.y, a.z, a.w}, dv[4] = {d.x, d.y, d.z, d.w};
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        float p = av[e];
-        if (mode == 0) {
-          const float r = av[e] - dv[e];
-          p = r > 0.f ? r : 0.f;
-        }
-        run += fixed_weight(p);
-        if (!done && run > t) {
-          found = v + e;
-          done = true;
-        }
-      }
-    }
-  } else {
-    for (int v = v0; v < v1; ++v) {
-      run += row_weight(pt, pd, v, mode);
-      if (!done && run > t) {
-        found = v;
-        done = true;
+        left -= tile;
       }
     }
   }
   return found;
 }
 
-template <bool KEEP>
 __global__ __launch_bounds__(kThreads) void spec_sample_kernel(const int32_t* __restrict__ draft_tokens,
                                                                const float* __restrict__ p_draft,
                                                                const float* __restrict__ p_target,
@@ -197,8 +158,11 @@ __global__ __launch_bounds__(kThreads) void spec_sample_kernel(const int32_t* __
                                                                int32_t* __restrict__ accept_len,
                                                                int32_t* __restrict__ next_token) {
   const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const float* u = uniforms + (size_t)b * (gamma + 1);
+  const float draw = u[gamma];
   __shared__ int first_reject;
+  __shared__ uint64_t wave_sum[kWaves];
 
   // Acceptance tests of every position (gamma <= 64: wave 0).
   if (tid < 64) {
@@ -214,22 +178,37 @@ __global__ __launch_bounds__(kThreads) void spec_sample_kernel(const int32_t* __
     if (lane == 0) first_reject = rej ? __ffsll((long long)rej) - 1 : gamma;
   }
   __syncthreads();
-  const int j = first_reject;
+  const int j = __builtin_amdgcn_readfirstlane(first_reject);
   const float* pt = p_target + ((size_t)b * (gamma + 1) + j) * V;
   const float* pd = p_draft + ((size_t)b * gamma + (j < gamma ? j : 0)) * V;
-
-  // Contiguous chunks of a multiple of 4 tokens per thread; with V % 4 == 0
-  // and 16-byte aligned arrays every chunk is read with float4 loads.
-  const int chunk = ((V + 4 * kThreads - 1) / (4 * kThreads)) * 4;
-  const int v0 = min(V, tid * chunk), v1 = min(V, v0 + chunk);
   const bool vec = (V & 3) == 0 && ((((uintptr_t)p_target) | ((uintptr_t)p_draft)) & 15) == 0;
+
+  const int region = (V + kWaves * kTile - 1) / (kWaves * kTile) * kTile;  // tokens per wave
+  const int v0 = min(V, wave * region), v1 = min(V, v0 + region);
   int mode = j < gamma ? 0 : 1;
-  // KEEP (chunk <= kHeld): the chunk fits the LDS copy, so the rows are read once
-  __shared__ float held[KEEP ? kHeld * kThreads : 1];
-  uint64_t total = 0, mine = 0, before = 0;
+  float p[kTiles][4];
+  uint64_t total = 0, before = 0, mine = 0;
   for (int pass = 0; pass < 2; ++pass) {
-    mine = KEEP ? held_weight(held, pt, pd, v0, v1, mode, vec) : chunk_weight(pt, pd, v0, v1, mode, vec);
-    before = block_exclusive_scan(mine, &total);
+    mine = 0;
+    for (int g = v0; g < v1; g += kGroup) {
+      uint64_t s[kTiles];
+      load_group(p, pt, pd, g, v1, mode, vec, lane);
+      group_weights(p, s);
+#pragma unroll
+      for (int t = 0; t < kTiles; ++t) mine += s[t];
+    }
+#pragma unroll
+    for (int m = 1; m < 64; m <<= 1) mine += shfl_xor_u64(mine, m);
+    if (lane == 0) wave_sum[wave] = mine;
+    __syncthreads();
+    total = before = 0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+      const uint64_t s = wave_sum[w];
+      if (w < wave) before += s;
+      total += s;
+    }
+    __syncthreads();  // wave_sum is reused by the next pass
     if (total > 0 || mode == 1) break;
     mode = 1;  // a residual of zero weight: draw from the target row itself
   }
@@ -240,12 +219,15 @@ __global__ __launch_bounds__(kThreads) void spec_sample_kernel(const int32_t* __
     }
     return;
   }
-  uint64_t t = (uint64_t)((double)u[gamma] * (double)total);
+  uint64_t t = (uint64_t)((double)draw * (double)total);
   if (t >= total) t = total - 1;
-  if (before <= t && t < before + mine) {
-    accept_len[b] = j;
-    // the owner reads back its own LDS entries (no barrier needed)
-    next_token[b] = KEEP ? held_find(held, v0, v1, before, t) : chunk_find(pt, pd, v0, v1, mode, vec, before, t);
+  if (t < before || t >= before + mine) return;
+  if (lane == 0) accept_len[b] = j;
+  uint64_t left = t - before;
+  for (int g = v0; g < v1; g += kGroup) {
+    // a region of one group is still in registers
+    if (region > kGroup) load_group(p, pt, pd, g, v1, mode, vec, lane);
+    if (find_in_group(p, g, left, lane, next_token + b)) return;
   }
 }
 
@@ -254,13 +236,8 @@ __global__ __launch_bounds__(kThreads) void spec_sample_kernel(const int32_t* __
 hipError_t launch_spec_sample(const int32_t* draft_tokens, const float* p_draft, const float* p_target,
                               const float* uniforms, int B, int gamma, int V, int32_t* accept_len,
                               int32_t* next_token, hipStream_t stream) {
-  const int chunk = ((V + 4 * kThreads - 1) / (4 * kThreads)) * 4;
-  if (chunk <= kHeld)
-    hipLaunchKernelGGL(spec_sample_kernel<true>, dim3(B), dim3(kThreads), 0, stream, draft_tokens, p_draft,
-                       p_target, uniforms, gamma, V, accept_len, next_token);
-  else
-    hipLaunchKernelGGL(spec_sample_kernel<false>, dim3(B), dim3(kThreads), 0, stream, draft_tokens, p_draft,
-                       p_target, uniforms, gamma, V, accept_len, next_token);
+  hipLaunchKernelGGL(spec_sample_kernel, dim3(B), dim3(kThreads), 0, stream, draft_tokens, p_draft, p_target,
+                     uniforms, gamma, V, accept_len, next_token);
   return hipGetLastError();
 }
 

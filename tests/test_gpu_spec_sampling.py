@@ -92,3 +92,35 @@ def test_uniform_sweep_boundaries():
     want_acc, want_tok = S.spec_sample_verify(tokens, pdB, ptB, u)
     assert np.array_equal(acc.cpu().numpy(), want_acc) and (want_acc == 1).all()
     assert np.array_equal(tok.cpu().numpy(), want_tok)
+
+
+@pytest.mark.parametrize("V", [4, 257, 4096, 4099, 32000, 40001])
+def test_certain_rows(V):
+    """Rows that put all their mass on one token (probability exactly 1: its
+    weight 2^32 needs more than 32 bits), at the first, a middle and the last
+    token, and rows of two tokens half and half across a lane, tile or region
+    boundary; the draft never proposes the target's token, so every chain is
+    rejected at once and draws from the residual."""
+    require_gpu()
+    at = sorted({0, 3, V // 2, V - 1, min(V - 1, 255), min(V - 1, 2047)})
+    rows = [(a, a) for a in at] + [(a, min(a + 1, V - 1)) for a in at]
+    B, gamma = 2 * len(rows), 1
+    pd = np.zeros((B, gamma, V), dtype=np.float32)
+    pt = np.zeros((B, gamma + 1, V), dtype=np.float32)
+    tokens = np.zeros((B, gamma), dtype=np.int32)
+    for b in range(B):
+        lo, hi = rows[b // 2]
+        pt[b, :, lo] += 0.5
+        pt[b, :, hi] += 0.5
+        tokens[b, 0] = next(t for t in range(V) if t not in (lo, hi))
+        pd[b, 0, tokens[b, 0]] = 1.0
+    u = np.tile(np.array([[0.3, 0.25], [0.3, 0.75]], dtype=np.float32), (B // 2, 1))
+    dev = torch.device("cuda")
+    acc = torch.full((B,), -7, dtype=torch.int32, device=dev)
+    tok = torch.full((B,), -7, dtype=torch.int32, device=dev)
+    glide.spec_sample_verify(torch.from_numpy(tokens).to(dev), torch.from_numpy(pd).to(dev),
+                             torch.from_numpy(pt).to(dev), torch.from_numpy(u).to(dev), acc, tok)
+    torch.cuda.synchronize()
+    want_acc, want_tok = S.spec_sample_verify(tokens, pd, pt, u)
+    assert np.array_equal(acc.cpu().numpy(), want_acc) and (want_acc == 0).all()
+    assert np.array_equal(tok.cpu().numpy(), want_tok)
