@@ -34,35 +34,50 @@ __device__ __forceinline__ uint64_t shfl_u64(uint64_t v, int src) {
   return ((uint64_t)hi << 32) | lo;
 }
 
-__device__ __forceinline__ uint64_t wave_max_u64(uint64_t v) {
-#pragma unroll
-  for (int m = 32; m > 0; m >>= 1) {
-    const uint32_t lo = __shfl_xor((uint32_t)v, m), hi = __shfl_xor((uint32_t)(v >> 32), m);
-    const uint64_t o = ((uint64_t)hi << 32) | lo;
-    v = o > v ? o : v;
-  }
-  return v;
+__device__ __forceinline__ uint64_t readlane_u64(uint64_t v, int lane) {
+  const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)v, lane), hi = __builtin_amdgcn_readlane((uint32_t)(v >> 32), lane);
+  return ((uint64_t)hi << 32) | lo;
+}
+
+// Max over a wave, in every lane: within the 16-lane DPP rows (neighbours,
+// pairs, half mirror, mirror), then across the rows.
+template <int CTRL>
+__device__ __forceinline__ int row_swap(int v) {
+  return __builtin_amdgcn_mov_dpp(v, CTRL, 0xF, 0xF, true);
+}
+
+__device__ __forceinline__ int wave_max(int v) {
+  v = max(v, row_swap<0xB1>(v));
+  v = max(v, row_swap<0x4E>(v));
+  v = max(v, row_swap<0x141>(v));
+  v = max(v, row_swap<0x140>(v));
+  return max(max(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16)),
+             max(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48)));
 }
 
 __global__ __launch_bounds__(64 * kWaves) void verify_commit_kernel(CommitArgs args, int slabs_per_wg) {
   const int b = blockIdx.y;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int N = args.N;
   const int32_t* ta = args.target_argmax + (size_t)b * (N + 1);
 
   // Acceptance: node n is accepted iff every node on its root path matches.
-  int p = -1;
-  bool match = false;
+  // The ancestor masks need only the parents, so they are built while the
+  // candidates and the target's tokens are on their way; the doubling stops
+  // when every lane has reached its root (a tree of depth 6 takes three
+  // rounds, not six).  Bound: this chain of dependent steps (40 layers x 40
+  // heads of four sequences 8.2 us with the doubling behind the tokens and
+  // 64-bit shuffles for the maximum, 6.2 us now).
+  int p = -1, want = -1, token = 0;
   uint64_t anc = 0;
   if (lane < N) {
     p = args.parents[(size_t)b * N + lane];
+    token = args.cand[(size_t)b * N + lane];
     if (p < -1 || p >= lane) p = -1;
-    match = args.cand[(size_t)b * N + lane] == ta[p + 1];
+    want = ta[p + 1];
     anc = 1ull << lane;
   }
-  const uint64_t matched = __ballot(match);
-#pragma unroll
-  for (int round = 0; round < 6; ++round) {
+  for (int round = 0; round < 6 && __any(p >= 0); ++round) {
     const int src = p < 0 ? lane : p;
     const uint64_t a_up = shfl_u64(anc, src);
     const int p_up = __shfl(p, src);
@@ -71,12 +86,12 @@ __global__ __launch_bounds__(64 * kWaves) void verify_commit_kernel(CommitArgs a
       p = p_up;
     }
   }
+  const uint64_t matched = __ballot(lane < N && token == want);
   const bool accepted = lane < N && (anc & ~matched) == 0;
-  const int depth = __popcll(anc);
-  const uint64_t key = wave_max_u64(accepted ? (((uint64_t)depth << 8) | (uint64_t)(255 - lane)) : 0);
-  const int a = (int)(key >> 8);
-  const int last = key ? 255 - (int)(key & 255) : -1;
-  const uint64_t path_mask = last >= 0 ? shfl_u64(anc, last) : 0;
+  const int key = wave_max(accepted ? (__popcll(anc) << 8) | (255 - lane) : 0);
+  const int a = key >> 8;
+  const int last = key ? 255 - (key & 255) : -1;
+  const uint64_t path_mask = last >= 0 ? readlane_u64(anc, last) : 0;
   // slot (depth - 1) of every path node, and the node in every slot
   const bool on_path = (path_mask >> lane) & 1;
   const int rank = __popcll(path_mask & ((1ull << lane) - 1));
@@ -102,7 +117,7 @@ __global__ __launch_bounds__(64 * kWaves) void verify_commit_kernel(CommitArgs a
       if (lane >= a && lane < N) args.path[(size_t)b * N + lane] = -1;
     }
   }
-  __syncthreads();
+  __builtin_amdgcn_wave_barrier();  // node_of: each wave reads its own
   if (a == 0 || args.layers == 0) return;
 
   const int H = args.H, R = args.row_bytes;     // 256 (bf16) or 512 (fp32)
@@ -111,7 +126,7 @@ __global__ __launch_bounds__(64 * kWaves) void verify_commit_kernel(CommitArgs a
   const int chunk = lane % lanes_per_row, q = lane / lanes_per_row;
   const int s_begin = blockIdx.x * slabs_per_wg;
   const int s_end = min(args.layers * H, s_begin + slabs_per_wg);
-  const int w = __builtin_amdgcn_readfirstlane(wave);
+  const int w = wave;
   const int mine = s_end > s_begin + w ? (s_end - s_begin - w + kWaves - 1) / kWaves : 0;
   const int upr = (a + rows_per_load - 1) / rows_per_load;  // load units per slab
 

@@ -208,3 +208,21 @@ def test_cape_candidate_threshold(V, rows):
     assert np.array_equal(tok.cpu().numpy(), w_tok)
     assert np.array_equal(par.cpu().numpy(), w_par)
     assert np.array_equal(nn.cpu().numpy(), w_n)
+
+
+@pytest.mark.parametrize("V", [1, 63, 4096, 32000, 32772, 50001])
+@pytest.mark.parametrize("rows", [20, 600])
+def test_argmax_masked_rows(V, rows):
+    """Rows of -inf but for a few tokens (as logit masks leave them), rows of
+    -inf only (index 0), and maxima that repeat across threads and waves, in
+    both launch sizes."""
+    require_gpu()
+    rng = np.random.default_rng(V)
+    x = np.full((rows, V), -np.inf, dtype=np.float32)
+    for r in range(1, rows):
+        kept = rng.integers(0, V, size=1 + r % 7)
+        x[r, kept] = rng.integers(-3, 0, size=kept.shape[0])
+    idx = torch.full((rows,), -7, dtype=torch.int32, device="cuda")
+    glide.glide_argmax_rows(torch.from_numpy(x).cuda(), idx)
+    torch.cuda.synchronize()
+    assert np.array_equal(idx.cpu().numpy(), np.argmax(x, axis=1))
