@@ -676,7 +676,17 @@ __device__ __forceinline__ void merge_partials(const AttnArgs& a, int b, int h, 
 // (33B and long-context shapes: -6 %).  Otherwise sequence y.  Ranks of
 // raw lengths form a permutation, so every sequence is still taken exactly
 // once and the results do not depend on the order.
-__device__ __forceinline__ int seq_of_row(const int32_t* seq_lens, int B, int splits, int y, int lane) {
+//
+// Grids of at most `paired` workgroups are resident at once, two on a CU from
+// the 257th workgroup on, and a CU's pair shares what it can stream.  The
+// rows behind the first round of CUs are then taken shortest first, so that
+// the longest sequences share with the shortest instead of with the middle
+// ones: 16 sequences x 32 heads of 1024..4096 keys, 5 rows 125 -> 110 us, of
+// 16K..32K keys 1040 -> 961 us, float32 (16 rows) 249 -> 218 us.  Past 512
+// workgroups the order is longest first throughout (1024 of them: 224 us
+// against 240).
+__device__ __forceinline__ int seq_of_row(const int32_t* seq_lens, int B, int H, int splits, int paired, int y,
+                                          int lane) {
   if (splits != 1 || B < 2 || B > 64) return y;
   const int len = lane < B ? seq_lens[lane] : 0;
   int rank = 0;
@@ -684,6 +694,8 @@ __device__ __forceinline__ int seq_of_row(const int32_t* seq_lens, int B, int sp
     const int lj = __shfl(len, j);
     rank += (lj > len) || (lj == len && j < lane);
   }
+  const int first = kNumCU / H;  // rows that start on CUs of their own
+  if (B * H <= paired && y >= first) y = first + B - 1 - y;
   const uint64_t hit = __ballot(lane < B && rank == y);
   return __builtin_amdgcn_readfirstlane(__ffsll((long long)hit) - 1);
 }
@@ -716,7 +728,9 @@ void tree_attn_kernel(AttnArgs args) {
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int h = blockIdx.x, s = blockIdx.z;
-  const int b = seq_of_row(args.seq_lens, args.B, args.splits, blockIdx.y, lane);
+  // two query tiles take a SIMD's whole register file: one workgroup per CU
+  constexpr int kPaired = NT == 1 ? 2 * kNumCU : 0;
+  const int b = seq_of_row(args.seq_lens, args.B, args.H, args.splits, kPaired, blockIdx.y, lane);
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int c = lane & 15, g = lane >> 4;
   const int qg = wave / kWpg, wig = wave % kWpg;  // query group, wave in group
@@ -974,7 +988,11 @@ void tree_attn_shared_kernel(AttnArgs args) {
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int h = blockIdx.x, s = blockIdx.z;
-  const int b = seq_of_row(args.seq_lens, args.B, args.splits, blockIdx.y, lane);
+  // Longest first throughout: pairing gains nothing here (16 x 32 heads, 64
+  // rows of 16K..32K keys 1010 against 1018 us paired, 8 x 52 heads of
+  // 4096..8192 keys 227 either way).
+  constexpr int kPaired = 0;
+  const int b = seq_of_row(args.seq_lens, args.B, args.H, args.splits, kPaired, blockIdx.y, lane);
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int c = lane & 15, g = lane >> 4;
   const int tile = wave % TQ, phase = wave / TQ;

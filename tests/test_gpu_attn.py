@@ -113,6 +113,21 @@ def test_empty_cross_key_set_is_zero():
     assert not got.any()
 
 
+@pytest.mark.parametrize("B,H", [(2, 200), (5, 52), (9, 32), (16, 32), (17, 32), (64, 8), (64, 9), (3, 300)])
+@pytest.mark.parametrize("N,dtype", [(5, torch.bfloat16), (20, torch.bfloat16), (5, torch.float32)])
+def test_one_split_row_order(B, H, N, dtype):
+    """One-split batches whose workgroups fill the CUs in part, twice, or more
+    (longest-first rows, the rows behind the first 256 workgroups reversed up
+    to 512): every sequence is taken once, ties in length included."""
+    lens = [(7 * b) % 23 for b in range(B)]
+    got, ref = run_case(B, N, H, lens, "random", dtype, 1, 90 + B)
+    # Few keys: outputs are as large as single value rows (|v| up to 4), so
+    # bf16 adds its two roundings to 8 significant bits, of the probabilities
+    # and of the output, 2^-9 of the value each.
+    bound = BF16_TOL + 2.0 ** -8 * np.abs(ref) if dtype == torch.bfloat16 else F32_TOL
+    assert (np.abs(got - ref) <= bound).all()
+
+
 def test_ragged_l_cap_slack():
     """L_cap well above the longest prefix: the unused rows are never read."""
     require_gpu()
