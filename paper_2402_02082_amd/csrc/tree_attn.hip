@@ -96,8 +96,10 @@ __device__ __forceinline__ uint64_t shfl_u64(uint64_t v, int src) {
 // Ancestor-or-self bitmask of node `lane` (bit m set iff tree node m is the
 // node itself or one of its ancestors), from that node's parent index.
 // Pointer doubling: after round r the mask covers ancestors closer than 2^r
-// and `p` points 2^r levels up; six rounds cover any depth <= 64.  Parents
-// outside [-1, lane) count as -1.
+// and `p` points 2^r levels up; six rounds cover any depth <= 64, and it
+// stops when every node has reached its root (three rounds for a depth of 5:
+// each is two dependent LDS round trips on the way to the tree rows' scores).
+// Parents outside [-1, lane) count as -1.
 __device__ __forceinline__ uint64_t ancestor_mask_from(int p, int N, int lane) {
   uint64_t a = 0;
   if (lane < N) {
@@ -106,8 +108,7 @@ __device__ __forceinline__ uint64_t ancestor_mask_from(int p, int N, int lane) {
   } else {
     p = -1;
   }
-#pragma unroll
-  for (int round = 0; round < 6; ++round) {
+  for (int round = 0; round < 6 && __any(p >= 0); ++round) {
     const int src = p < 0 ? lane : p;
     const uint64_t a_up = shfl_u64(a, src);
     const int p_up = __shfl(p, src);
@@ -264,6 +265,19 @@ __device__ __forceinline__ void load_kv(F32Path::KV& f, const char* kslab, const
 #pragma unroll
     for (int h = 0; h < 2; ++h)
       f.v[r][h] = __builtin_bit_cast(f32x4_t, load16<CPOL>(rv, o.v0 + 512 * r + 256 * h));
+}
+
+// Zero the value rows at or past k_end of a step that starts at key j0.
+__device__ __forceinline__ void clear_rows_past(Bf16Path::KV& f, int j0, int k_end, int g) {
+#pragma unroll
+  for (int i = 0; i < 8; ++i)
+    if (j0 + Bf16Path::key_slot(g, i) >= k_end) f.v[i] = u32x4_t{0, 0, 0, 0};
+}
+
+__device__ __forceinline__ void clear_rows_past(F32Path::KV& f, int j0, int k_end, int g) {
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+    if (j0 + 4 * g + r >= k_end) f.v[r][0] = f.v[r][1] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 }
 
 // Online-softmax state of one 16-query tile for the lane's query column.
@@ -770,10 +784,16 @@ void tree_attn_kernel(AttnArgs args) {
   const int k_end = min(T, k_begin + args.chunk);
   const int nsteps = first < k_end ? (k_end - first + kStride - 1) / kStride : 0;
   if (k_end < full_end) {
-    // The split ends inside the cache: fetch again so that rows past the
-    // sequence (possibly never written) read as zeros.
+    // The split ends inside the cache: rows past the sequence (possibly never
+    // written) were fetched too.  Their scores are masked, and their values
+    // are cleared here.  (Fetching the steps again from the shorter range cost
+    // every such split a second memory round trip before its first product,
+    // and one-split batches the bytes of two steps a wave.)
 #pragma unroll
-    for (int u = 0; u < kBufs; ++u) load_kv<Task::kCpol>(buf[u], kslab, vslab, first + u * kStride, k_end, lo);
+    for (int u = 0; u < kBufs; ++u) {
+      const int j0 = first + u * kStride;
+      if (j0 + kStep > k_end) clear_rows_past(buf[u], j0, k_end, g);
+    }
   }
 
   // Ancestor masks are only needed by the split that holds the tree rows.
@@ -1062,12 +1082,7 @@ void tree_attn_shared_kernel(AttnArgs args) {
     if (tile_live && j0 < k_end) {
       Bf16Path::KV f;
       read_step(f, ring + (t % kStages) * kStepBytes, c, g);
-      if (j0 + 32 > k_end) {
-        // rows past the split were not written by this round's loads
-#pragma unroll
-        for (int i = 0; i < 8; ++i)
-          if (j0 + Bf16Path::key_slot(g, i) >= k_end) f.v[i] = u32x4_t{0, 0, 0, 0};
-      }
+      if (j0 + 32 > k_end) clear_rows_past(f, j0, k_end, g);  // not written by this round's loads
       step<1, TREE>(f, qf, sm, acc, j0, Lb, k_end, N, anc, args.scale_log2, g);
     }
   }
@@ -1400,11 +1415,7 @@ void block_attn_kernel(BlockAttnArgs args) {
         if (any_live) {
           Bf16Path::KV f;
           read_step(f, ring + u * kStepBytes, c, g);
-          if (j0 + 32 > k_end) {
-#pragma unroll
-            for (int i = 0; i < 8; ++i)
-              if (j0 + Bf16Path::key_slot(g, i) >= k_end) f.v[i] = u32x4_t{0, 0, 0, 0};
-          }
+          if (j0 + 32 > k_end) clear_rows_past(f, j0, k_end, g);
           block_step<kNT>(f, qf, sm, acc, j0, tile_lo, my_limit, args.scale_log2, g);
         }
       }

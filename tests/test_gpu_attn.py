@@ -128,6 +128,34 @@ def test_one_split_row_order(B, H, N, dtype):
     assert (np.abs(got - ref) <= bound).all()
 
 
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32], ids=["bf16", "f32"])
+@pytest.mark.parametrize("B,N,lens,kind,splits", [
+    (1, 5, [517], "chain", 5), (1, 16, [2048], "cape", 8), (1, 16, [130], "cape", 1), (2, 9, [0, 257], "random", 0),
+    (3, 5, [0, 31, 300], None, 1), (2, 16, [96, 1000], None, 3), (2, 40, [33, 290], "random", 2)])
+def test_rows_past_the_sequence_are_never_used(B, N, lens, kind, splits, dtype):
+    """Cache rows past the sequence hold NaN, and the cache reaches well past
+    it: splits that end inside the cache fetch such rows before they know the
+    length, and must not let them into a score or a sum."""
+    require_gpu()
+    H, tree = 3, kind is not None
+    L_cap = max(lens) + (N if tree else 0) + 600
+    q = cpu_normal((B, N, H, D), 31, dtype)
+    k, v = cpu_normal((B, H, L_cap, D), 32, dtype), cpu_normal((B, H, L_cap, D), 33, dtype)
+    parents = _parents(kind, B, N, 34)
+    ref = OA.tree_attention(to64(q), to64(k), to64(v), lens, parents)
+    for b in range(B):
+        end = lens[b] + (N if tree else 0)
+        k[b, :, end:] = float("nan")
+        v[b, :, end:] = float("nan")
+    out = torch.full((B, N, H, D), float("nan"), dtype=dtype, device="cuda")
+    glide.glide_tree_attn(q.cuda(), k.cuda(), v.cuda(), torch.tensor(lens, dtype=torch.int32, device="cuda"),
+                          None if parents is None else torch.from_numpy(parents).cuda(), out, max_splits=splits)
+    torch.cuda.synchronize()
+    # the row-size bound of test_one_split_row_order: short sequences
+    bound = BF16_TOL + 2.0 ** -8 * np.abs(ref) if dtype == torch.bfloat16 else F32_TOL
+    assert (np.abs(to64(out) - ref) <= bound).all()
+
+
 def test_ragged_l_cap_slack():
     """L_cap well above the longest prefix: the unused rows are never read."""
     require_gpu()
