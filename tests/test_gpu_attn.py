@@ -129,6 +129,18 @@ def test_one_split_row_order(B, H, N, dtype):
 
 
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32], ids=["bf16", "f32"])
+@pytest.mark.parametrize("B,N,H,L", [(1, 5, 1, 8000), (1, 16, 8, 4100), (1, 32, 20, 2500), (3, 5, 20, 1300),
+                                     (2, 8, 64, 700), (1, 16, 129, 600), (1, 33, 8, 2000)])
+def test_automatic_splits_of_few_heads(B, N, H, L, dtype):
+    """The automatic split plan on both sides of its rules (two workgroups per
+    head on CUs of their own or not, up to 32 rows or more, one to eight
+    merge batches): as close to the oracle as ever, and the workspace it asks
+    for is enough."""
+    got, ref = run_case(B, N, H, [L - 7 * b for b in range(B)], "cape", dtype, 0, 50 + H)
+    assert np.abs(got - ref).max() <= (BF16_TOL if dtype == torch.bfloat16 else F32_TOL)
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32], ids=["bf16", "f32"])
 @pytest.mark.parametrize("B,N,lens,kind,splits", [
     (1, 5, [517], "chain", 5), (1, 16, [2048], "cape", 8), (1, 16, [130], "cape", 1), (2, 9, [0, 257], "random", 0),
     (3, 5, [0, 31, 300], None, 1), (2, 16, [96, 1000], None, 3), (2, 40, [33, 290], "random", 2)])
