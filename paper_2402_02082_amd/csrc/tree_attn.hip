@@ -1205,10 +1205,87 @@ constexpr int kSharedLds4 = 65536;
 constexpr int kSharedLds2 = 65536;
 
 
+// The block-masked kernel's value rows in LDS: unit (row, chunk) holds chunk
+// chunk ^ 2 * (row % 8), so that the 32-byte pieces of eight rows which 32
+// lanes of a transposing read take at once cover all banks.
+__device__ __forceinline__ int block_v_unit(int row, int chunk) { return row * 16 + (chunk ^ (2 * (row & 7))); }
+__device__ __forceinline__ int dma_block_v_off(int row, int lane) {
+  return row * 256 + 16 * ((lane & 15) ^ (2 * (row & 7)));
+}
+
+typedef short s16x4_t __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) s16x4_t* lds_s16x4_ptr_t;
+
+// Transposing LDS read: 16 lanes take four rows of 16 values, lane i at row
+// i / 4, values 4 * (i % 4) on, and lane i receives value i of the four rows.
+__device__ __forceinline__ uint2 read_transposed(const char* p) {
+  return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr_t)p));
+}
+
+// (a, b) with a's odd and b's even lane groups exchanged.
+__device__ __forceinline__ void swap_groups(float a, float b, float& lo, float& hi) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  lo = __uint_as_float(r[0]);
+  hi = __uint_as_float(r[1]);
+}
+
+// V^T operands of a step of the block-masked kernel: tile t holds head dim
+// 16t + c of the lane's eight keys (4g + r and 16 + 4g + r).  The restricted
+// pointer says that nothing writes these rows meanwhile: without it the
+// compiler waits for every load into the ring before the first read.
+__device__ __forceinline__ void read_block_v(u32x4_t (&vt)[8], const char* __restrict__ stepv, int c, int g) {
+  const int row = 4 * g + c / 4;
+#pragma unroll
+  for (int t = 0; t < 8; ++t) {
+    const char* p = stepv + 16 * block_v_unit(row, 2 * t + ((c >> 1) & 1)) + 8 * (c & 1);
+    const uint2 lo = read_transposed(p), hi = read_transposed(p + 16 * 256);
+    vt[t] = u32x4_t{lo.x, lo.y, hi.x, hi.y};
+  }
+}
+
+// Zero the keys at or past k_end in the V^T operands of a step at key j0.
+__device__ __forceinline__ void clear_keys_past(u32x4_t (&vt)[8], int j0, int k_end, int g) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int left = k_end - (j0 + 16 * (e / 2) + 4 * g + 2 * (e & 1));
+    const uint32_t keep = left >= 2 ? 0xffffffffu : left == 1 ? 0x0000ffffu : 0u;
+#pragma unroll
+    for (int t = 0; t < 8; ++t) vt[t][e] &= keep;
+  }
+}
+
+// K operands of a step of the block-masked kernel, and its scores against
+// the wave's NT query tiles.
+__device__ __forceinline__ void read_block_k(u32x4_t (&k)[2][4], const char* stepk, int c, int g) {
+#pragma unroll
+  for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+    for (int st = 0; st < 4; ++st) k[kt][st] = *(const u32x4_t*)(stepk + 16 * k_unit(16 * kt + c, 4 * st + g));
+}
+
+template <int NT>
+__device__ __forceinline__ void block_scores(const u32x4_t (&k)[2][4], const Bf16Path::QFrag (&qf)[NT],
+                                             f32x4_t (&s)[2][NT]) {
+#pragma unroll
+  for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+      f32x4_t a = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int st = 0; st < 4; ++st)
+        a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(k[kt][st]), as_bf16x8(qf[nt].v[st]), a, 0, 0, 0);
+      s[kt][nt] = a;
+    }
+}
+
 // One 32-key step of the block-masked kernel for the wave's NT query tiles.
 // That kernel is compute-bound (every step feeds 32 queries per wave) and
 // its vector-ALU work competes with the MFMA products for issue, so the
-// per-score vector work is cut down against the shared step:
+// vector work is cut down against the shared step:
+//  * the V^T operands come transposed out of LDS, which saves the 32 byte
+//    permutes of a step (about a quarter of its vector instructions; four
+//    sequences of 2048 positions, 32 heads, blocks of 5: 158.4 -> 149.5 us,
+//    870 -> 920 TFLOP/s);
 //  * masking runs only in the steps that reach tile 0's limit (the
 //    smallest, wave-uniform); each lane then masks against its own limit;
 //  * the reference max moves only when some lane's scaled score passes it by
@@ -1221,25 +1298,13 @@ constexpr int kSharedLds2 = 65536;
 //  * the masking and the rescale sit in one branch each for all tiles, so
 //    the common path is one straight block the scheduler can interleave.
 template <int NT>
-__device__ __forceinline__ void block_step(const Bf16Path::KV& f, const Bf16Path::QFrag (&qf)[NT],
+__device__ __forceinline__ void block_step(const u32x4_t (&k)[2][4], const u32x4_t (&vt)[8],
+                                           const Bf16Path::QFrag (&qf)[NT],
                                            SoftmaxState (&sm)[NT], f32x4_t (&acc)[NT][8], int j0,
                                            const int (&tile_lo)[NT], const int (&lim)[NT],
                                            float scale_log2, int g) {
   f32x4_t s[2][NT];
-#pragma unroll
-  for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-      f32x4_t a = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int st = 0; st < 4; ++st)
-        a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(f.k[kt][st]), as_bf16x8(qf[nt].v[st]),
-                                                    a, 0, 0, 0);
-      s[kt][nt] = a;
-    }
-
-  u32x4_t vt[8];
-  transpose_v(f.v, vt);
+  block_scores<NT>(k, qf, s);
 
   float x[NT][8];
 #pragma unroll
@@ -1313,7 +1378,10 @@ __device__ __forceinline__ void block_step(const Bf16Path::KV& f, const Bf16Path
 // sequence, 64 * kNT query positions), kNT 16-position tiles per wave (each
 // K/V step read out of LDS once feeds every tile's products), keys streamed
 // through the same LDS ring as the shared-step kernel, workgroups with the
-// most keys first.  Each lane (query) compares the keys against its own
+// most keys first.  Scores run one step ahead of the softmax (162 against 159
+// us), a meeting every second step (150.5 against 149.5), and three tiles per
+// wave (151.4; the last registers) gain nothing; four need a wave per SIMD
+// (240).  Each lane (query) compares the keys against its own
 // limit, in the steps that reach its tile's limits.
 // ---------------------------------------------------------------------------
 template <int kNT>
@@ -1373,7 +1441,7 @@ void block_attn_kernel(BlockAttnArgs args) {
   const char* vslab = (const char*)((const uint16_t*)args.v + head_off);
 
   const int dma_row = 4 * wave + (lane >> 4);
-  const int dma_off[2] = {dma_k_off(dma_row, lane), dma_v_off(dma_row, lane)};
+  const int dma_off[2] = {dma_k_off(dma_row, lane), dma_block_v_off(dma_row, lane)};
   auto issue_step = [&](int t, int stage_idx) {
     char* stage = ring + stage_idx * kStepBytes;
     const int j0 = 32 * t;
@@ -1409,30 +1477,36 @@ void block_attn_kernel(BlockAttnArgs args) {
     for (int u = 0; u < kStages; ++u) {
       const int t = t0 + u;
       if (t < steps) {
+        // every wave's reads of step t - 1, whose stage is loaded next, are complete
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         ring_wait_and_meet<(kStages - 2) * kStepInstr>();
         issue_step(t + kStages - 1, (u + kStages - 1) % kStages);
         const int j0 = 32 * t;
         if (any_live) {
-          Bf16Path::KV f;
-          read_step(f, ring + u * kStepBytes, c, g);
-          if (j0 + 32 > k_end) clear_rows_past(f, j0, k_end, g);
-          block_step<kNT>(f, qf, sm, acc, j0, tile_lo, my_limit, args.scale_log2, g);
+          u32x4_t k[2][4], vt[8];
+          read_block_k(k, ring + u * kStepBytes, c, g);
+          read_block_v(vt, ring + u * kStepBytes + kStepBytes / 2, c, g);
+          if (j0 + 32 > k_end) clear_keys_past(vt, j0, k_end, g);
+          block_step<kNT>(k, vt, qf, sm, acc, j0, tile_lo, my_limit, args.scale_log2, g);
         }
       }
     }
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  // acc[nt][t][r] is dim 16t + 4g + r.  Odd lane groups' values of even tiles
+  // change places with even groups' of odd tiles, so that a lane holds eight
+  // dims in a row of each tile pair.
 #pragma unroll
   for (int nt = 0; nt < kNT; ++nt) {
     const float L = sum_across_groups(sm[nt].l);
     const float inv = (L > 0.f) ? 1.f / L : 0.f;
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
+    for (int u = 0; u < 4; ++u) {
       float o[8];
 #pragma unroll
-      for (int t = 0; t < 8; ++t) o[t] = acc[nt][t][r] * inv;
+      for (int r = 0; r < 4; ++r) swap_groups(acc[nt][2 * u][r] * inv, acc[nt][2 * u + 1][r] * inv, o[r], o[4 + r]);
       if (p[nt] < T)
-        store_row8((uint16_t*)args.out + (((size_t)b * T + p[nt]) * H + h) * kD + 32 * g + 8 * r, o);
+        store_row8((uint16_t*)args.out + (((size_t)b * T + p[nt]) * H + h) * kD + 32 * u + 16 * (g & 1) + 8 * (g >> 1), o);
     }
   }
 }

@@ -98,3 +98,22 @@ def test_peaked_scores():
     got = to64(out)[:, pos]
     excess = np.abs(got - want[:, pos]) - (BF16_TOL + np.abs(want[:, pos]) / 256)
     assert float(excess.max()) <= 0, float(np.abs(got - want[:, pos]).max())
+
+
+@pytest.mark.parametrize("B,H", [(1, 2), (16, 32)])   # one and two tiles per wave
+@pytest.mark.parametrize("T", [2, 3, 4, 5, 6, 17, 18, 20, 32, 33, 34, 36])
+def test_last_step_of_any_length(B, H, T):
+    """Blocks of one position: the last of T - 1 keys falls on every place of
+    a lane's keys in a 32-key step.  A call over NaN values before it leaves
+    NaN in the places of the keys that the step does not have."""
+    require_gpu()
+    say("block_attn last step", dict(B=B, H=H, T=T))
+    nan = torch.full((B, H, 64, 128), float("nan"), dtype=torch.bfloat16, device="cuda")
+    q = torch.zeros((B, 64, H, 128), dtype=torch.bfloat16, device="cuda")
+    glide.glide_block_attn(q, nan, nan, torch.empty_like(q), 1)
+    err, got = _run(300 + T, B, T, H, T, 1, positions=sorted({0, 1, T // 2, T - 1}))
+    assert np.all(np.isfinite(got))
+    # Few keys: outputs are value rows (all below 6 here) rather than averages.
+    # The probabilities (they sum to 1) and the output each round to bf16, by
+    # at most 2^-9 of such a value.
+    assert err <= 2 * 6 / 512, err
