@@ -160,9 +160,8 @@ int glide_tree_attn(const void* q, const void* k_cache, const void* v_cache,
  * The call allocates nothing and records no memset: the array starts zeroed
  * when the library is loaded, every call leaves its counters zero, and the
  * partials are written before they are read.  Sizes whose split plan needs
- * more than the scratch holds return GLIDE_ESCRATCH before any HIP call (with
- * max_splits = 0 and more than 128 (sequence, head) pairs the plan takes
- * fewer splits instead, down to one); sizes that need no workspace
+ * more than the scratch holds (glide_tree_attn_workspace(...) > the maximum)
+ * return GLIDE_ESCRATCH before any HIP call; sizes that need no workspace
  * never touch it.
  * The first call on a device, with that device current, looks up the
  * scratch array's device address (hipGetSymbolAddress).

@@ -172,8 +172,7 @@ int tree_attn_call(const void* q, const void* k_cache, const void* v_cache, cons
   if (!tree_attn_sizes_ok(B, N, H, D, L_cap, tree)) return GLIDE_EINVAL;
   if (max_splits < 0 || max_splits > glide::kMaxSplits) return GLIDE_EINVAL;
   if (!isfinite(scale)) return GLIDE_EINVAL;
-  const glide::AttnPlan plan =
-      glide::plan_tree_attn(B, N, H, L_cap, max_splits, scratch ? kNoAllocScratchBytes : SIZE_MAX);
+  const glide::AttnPlan plan = glide::plan_tree_attn(B, N, H, L_cap, max_splits);
   if (scratch) {
     if (plan.ws_bytes > kNoAllocScratchBytes) return GLIDE_ESCRATCH;
     if (plan.ws_bytes > 0) {

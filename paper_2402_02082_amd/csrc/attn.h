@@ -38,9 +38,7 @@ struct AttnPlan {
   bool half_states;      // bf16 states exchanged as fp16 o / L (in-kernel merge, N >= 8)
 };
 
-// ws_limit: automatic plans of many (sequence, head) pairs take only split
-// counts whose states fit this many bytes.
-AttnPlan plan_tree_attn(int B, int N, int H, int L_cap, int max_splits, size_t ws_limit = SIZE_MAX);
+AttnPlan plan_tree_attn(int B, int N, int H, int L_cap, int max_splits);
 
 struct AttnArgs {
   const void* q;

@@ -1596,79 +1596,14 @@ static int few_heads_splits(long bh, int N, int keys) {
   return want;
 }
 
-// Splits when there are more than kNumCU / 2 (sequence, head) pairs: at most
-// kManyHeadsSplits, the least of the estimates below of the time (us) of a
-// bf16 call whose sequences fill the cache to about 80 % (between uniform
-// batches and ragged ones).  `most`: the largest count whose states the
-// caller can hold.
-//
-// Register kernel (up to 16 rows): the stream's share of 6.3 TB/s follows the
-// share of workgroup slots that the grid's last round fills -- 1.2 times it
-// unsplit, 1.08 times it split, where ragged batches lose to uneven pieces --
-// and a split adds the merge launch and its states' bytes; past 512 pairs one
-// split.  Shared-step kernel: 512 workgroups run at once, and a second one on
-// a CU adds more than it takes, so grids are filled to 512 where that
-// shortens the stream of one workgroup (keys times kShared*Us) by more than
-// the merge costs; past 256 pairs one split.
-//
-// The least split_cost took up to 64 splits for a slightly fuller last round.
-// Over 384 shapes (140..1024 pairs, 5..64 rows, 1024..8192 keys, uniform and
-// ragged down to a quarter) this is 6 % faster on average, e.g. uniform /
-// ragged: 288 pairs, 16 rows, 1024 keys 44.8 / 43.1 us, now 38.5 / 26.2; 260
-// pairs, 32 rows, 2048 keys 74 / 50, now 53 / 42; 240 pairs, 32 rows, 4096
-// keys 90 / 78, now 85 / 61; 160 pairs, 32 rows, 8192 keys 148 / 95, now 113 /
-// 80.  The worst loss is 140 pairs, 5 rows, 8192 keys: 106 / 83, now 108 / 95.
-constexpr int kManyHeadsSplits = 4;
-constexpr double kFill = 0.8;
-constexpr double kShared32Us = 0.0193, kShared64Us = 0.0222;  // a key of a lone workgroup, up to 32 / 64 rows
-
-static int many_heads_splits(long bh, int N, int keys, int most) {
-  const bool shared = N > 16;
-  if (bh > (shared ? 1 : 2) * kNumCU) return 1;
-  const double bytes = kFill * (double)bh * kv_bytes(keys);
-  double best = 0.0;
-  int want = 1;
-  for (int s = 1; s <= min(kManyHeadsSplits, most); ++s) {
-    const int chunk = chunk_of(keys, s), pieces = (keys + chunk - 1) / chunk;
-    const long grid = bh * pieces;
-    const double states = 2.0 * (double)grid * partial_bytes(N);
-    double t;
-    if (shared) {
-      if (grid > 2 * kNumCU) break;
-      const double alone = chunk * (N <= 32 ? kShared32Us : kShared64Us);
-      t = fmax(grid > kNumCU ? 1.36 * alone : alone, bytes / 6.4e6);
-      if (pieces > 1) t = (t + 4.5 + 1.5 * states / 5e6) * (N <= 32 ? 1.0 : 1.05);
-    } else {
-      const double filled = (double)grid / (double)((grid + kNumCU - 1) / kNumCU * kNumCU);
-      const double share = pieces == 1 ? fmin(1.05, 1.2 * filled) : fmin(1.0, 1.08 * filled);
-      t = bytes / 6.3e6 / share;
-      if (pieces > 1) t += 2.8 + 2.0 * states / 5e6;
-    }
-    if (s == 1 || t < 0.99 * best) best = t, want = s;
-  }
-  return want;
-}
-
-// Workspace bytes of a plan's split states (0 for one split).
-static size_t states_bytes(long bh, int N, int splits, bool half) {
-  if (splits == 1) return 0;
-  const size_t units = (size_t)bh * splits * N;
-  const size_t floats = ((kCounterBytes + units * sizeof(float2) + 255) & ~(size_t)255) + units * kHeadDim * sizeof(float);
-  return half ? ((floats + 255) & ~(size_t)255) + units * kHeadDim * sizeof(uint16_t) : floats;
-}
-
-AttnPlan plan_tree_attn(int B, int N, int H, int L_cap, int max_splits, size_t ws_limit) {
+AttnPlan plan_tree_attn(int B, int N, int H, int L_cap, int max_splits) {
   AttnPlan p{};
   const int keys = L_cap;  // upper bound on the keys any query sees
   const long bh = (long)B * H;
   int want;
   if (max_splits > 0) {
     want = max_splits;
-  } else if (2 * bh > kNumCU) {
-    int most = kManyHeadsSplits;
-    while (most > 1 && states_bytes(bh, N, most, B == 1 && N >= 8) > ws_limit) --most;
-    want = many_heads_splits(bh, N, keys, most);
-  } else if (N <= 32) {
+  } else if (2 * bh <= kNumCU && N <= 32) {
     want = few_heads_splits(bh, N, keys);
   } else {
     // Split only where it balances the CUs clearly better (a fifth less

@@ -111,6 +111,45 @@ def test_tree_attn_workspace_plan(lib):
     assert sizes == sorted(sizes)
 
 
+def _least_cost_splits(B, N, H, L_cap):
+    """The split count of the automatic plan: rounds of workgroups over the 256
+    CUs per unit of work, inflated by the split states' share of the K/V bytes,
+    at least 128 keys a split; one split unless that saves a fifth."""
+    def cost(s):
+        states = 2.0 * s * (N * 130 * 4) / (L_cap * 512) if s > 1 else 0.0
+        return -(-B * H * s // 256) / s * (1.0 + states)
+
+    best, want = cost(1), 1
+    for s in range(2, min(64, -(-L_cap // 128)) + 1):
+        if cost(s) < best - 1e-9:
+            best, want = cost(s), s
+    return 1 if best > 0.8 * cost(1) else want
+
+
+PLANNED = [(17, 8), (7, 20), (3, 52), (4, 40), (9, 20), (6, 32), (4, 52), (12, 20), (8, 32), (5, 52), (9, 32),
+           (8, 40), (10, 40), (8, 52), (16, 32), (11, 52), (20, 32), (16, 52), (32, 32), (1, 160), (1, 400)]
+
+
+@pytest.mark.parametrize("B,H", PLANNED)
+def test_automatic_plan_is_least_cost(lib, B, H):
+    """glide_tree_attn_workspace of automatic plans, over caches of 100 to
+    32000 rows and 1 to 64 queries: no split states where one split is taken
+    (so nothing passes through fp16 there), and the least-cost count's
+    otherwise."""
+    for N in (1, 5, 8, 16, 17, 32, 33, 64):
+        for L_cap in (100, 320, 576, 1088, 2112, 4160, 6200, 8256, 16448, 32000):
+            want = lib.glide_tree_attn_workspace(B, N, H, 128, L_cap, _least_cost_splits(B, N, H, L_cap))
+            assert lib.glide_tree_attn_workspace(B, N, H, 128, L_cap, 0) == want, (N, L_cap)
+
+
+@pytest.mark.parametrize("B,N,H,L_cap", [(11, 32, 52, 4160), (9, 64, 32, 4160), (5, 48, 52, 8256)])
+def test_noalloc_refuses_what_its_workspace_query_says(lib, B, N, H, L_cap):
+    """glide_tree_attn_noalloc takes glide_tree_attn's plan, so automatic plans
+    past the scratch are refused, with no HIP call before."""
+    assert lib.glide_tree_attn_workspace(B, N, H, 128, L_cap, 0) > lib.glide_tree_attn_noalloc_max_workspace()
+    assert _noalloc(lib, B=B, N=N, H=H, L_cap=L_cap) == glide.GLIDE_ESCRATCH
+
+
 def test_tree_attn_workspace_layout(lib):
     """A split workspace is the fixed 256 KiB counter block, then the (max,
     sum) pair and the 128-float output of every (sequence, head, split,

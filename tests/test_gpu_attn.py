@@ -132,11 +132,11 @@ def test_one_split_row_order(B, H, N, dtype):
 @pytest.mark.parametrize("B,N,H,L", [(1, 5, 1, 8000), (1, 16, 8, 4100), (1, 32, 20, 2500), (3, 5, 20, 1300),
                                      (2, 8, 64, 700), (1, 16, 129, 600), (1, 33, 8, 2000),
                                      (9, 5, 29, 900), (2, 64, 104, 600), (3, 20, 64, 500), (4, 40, 65, 300)])
-def test_automatic_splits_of_few_heads(B, N, H, L, dtype):
-    """The automatic split plan on both sides of its rules (up to 128, 256 and
-    512 (sequence, head) pairs or more, up to 16 and 32 rows or more, one to
-    eight merge batches): as close to the oracle as ever, and the workspace it
-    asks for is enough."""
+def test_automatic_splits(B, N, H, L, dtype):
+    """The automatic split plan from one to 416 (sequence, head) pairs, with one
+    split, a merge inside the kernel and a merge launch, one to eight merge
+    batches: as close to the oracle as ever, and the workspace it asks for is
+    enough."""
     got, ref = run_case(B, N, H, [L - 7 * b for b in range(B)], "cape", dtype, 0, 50 + H)
     assert np.abs(got - ref).max() <= (BF16_TOL if dtype == torch.bfloat16 else F32_TOL)
 
