@@ -1551,49 +1551,14 @@ hipError_t launch_nt(const AttnArgs& args, hipStream_t stream) {
 
 }  // namespace
 
-static double kv_bytes(int L_cap) { return (double)L_cap * kHeadDim * 2 * 2; }               // K and V, bf16
-static double partial_bytes(int N) { return (double)N * (kHeadDim + 2) * sizeof(float); }  // one split's partials
-
 // Relative cost of s splits: the grid runs in ceil(B*H*s / CUs) waves of
 // workgroups, each 1/s of a sequence long, and every split adds its partial
 // results (written once, read once by the merge) to the K/V stream.
 static double split_cost(long bh, int s, int N, int L_cap) {
-  const double kv = kv_bytes(L_cap), part = partial_bytes(N);
+  const double kv = (double)L_cap * kHeadDim * 2 * 2;                // K and V, bf16
+  const double part = (double)N * (kHeadDim + 2) * sizeof(float);  // one split's partials
   const double waves = (double)((bh * s + kNumCU - 1) / kNumCU);
   return waves / s * (1.0 + (s > 1 ? 2.0 * s * part / kv : 0.0));
-}
-
-// Keys per split, rounded up to whole quanta.
-static int chunk_of(int keys, int s) {
-  const int per = (keys + s - 1) / s;
-  return max((per + kChunkQuantum - 1) / kChunkQuantum * kChunkQuantum, kChunkQuantum);
-}
-
-// Splits of up to 32 query rows when at least two workgroups per (sequence,
-// head) fit on CUs of their own: at most one workgroup per CU, and within
-// that the fewest keys streamed by a workgroup -- inflated by the partial
-// states' bytes, as in split_cost -- plus what a split costs the merge, about
-// as much as 16 keys of the stream (the in-kernel merge reads eight splits'
-// states at a time).  A second workgroup on some CUs costs more than the
-// shorter pieces save (three sequences x 20 heads, 5 rows, 2048 keys: 16.1 us
-// at 4 splits, 21.8 at 9), and so do more splits than the stream needs (8
-// heads, 16 rows, 4096 keys: 11.2 us at 16 splits, 13.0 at 26).  Over 105
-// shapes it changes (8..128 heads x sequences, 1024..16384 keys) 8 % faster
-// than the least split_cost on average; from 33 rows on, where a second
-// workgroup on a CU does help, it loses up to 16 % (8 heads, 64 rows, 256
-// keys) and split_cost stays.
-static int few_heads_splits(long bh, int N, int keys) {
-  const int most = (int)min((long)min(kMaxSplits, (keys + kMinChunk - 1) / kMinChunk), kNumCU / bh);
-  const double part_of_kv = partial_bytes(N) / kv_bytes(keys);
-  double best = 0.0;
-  int want = 1;
-  for (int s = 1; s <= most; ++s) {
-    const int chunk = chunk_of(keys, s), pieces = (keys + chunk - 1) / chunk;
-    const int merged = N <= 16 && pieces > 8 ? (pieces + 7) / 8 * 8 : pieces;
-    const double cost = pieces == 1 ? chunk : chunk * (1.0 + 2.0 * pieces * part_of_kv) + 16.0 * merged;
-    if (s == 1 || cost < best) best = cost, want = s;
-  }
-  return want;
 }
 
 AttnPlan plan_tree_attn(int B, int N, int H, int L_cap, int max_splits) {
@@ -1603,8 +1568,6 @@ AttnPlan plan_tree_attn(int B, int N, int H, int L_cap, int max_splits) {
   int want;
   if (max_splits > 0) {
     want = max_splits;
-  } else if (2 * bh <= kNumCU && N <= 32) {
-    want = few_heads_splits(bh, N, keys);
   } else {
     // Split only where it balances the CUs clearly better (a fifth less
     // cost), taking the fewest splits that reach the best cost, and keep
@@ -1620,7 +1583,9 @@ AttnPlan plan_tree_attn(int B, int N, int H, int L_cap, int max_splits) {
     if (best > 0.8 * one) want = 1;
   }
   want = max(1, min(want, kMaxSplits));
-  p.chunk = chunk_of(keys, want);
+  int chunk = (keys + want - 1) / want;
+  chunk = ((chunk + kChunkQuantum - 1) / kChunkQuantum) * kChunkQuantum;
+  p.chunk = max(chunk, kChunkQuantum);
   p.splits = max(1, (keys + p.chunk - 1) / p.chunk);
   if (p.splits == 1) {
     p.ws_bytes = 0;

@@ -126,8 +126,10 @@ def _least_cost_splits(B, N, H, L_cap):
     return 1 if best > 0.8 * cost(1) else want
 
 
-PLANNED = [(17, 8), (7, 20), (3, 52), (4, 40), (9, 20), (6, 32), (4, 52), (12, 20), (8, 32), (5, 52), (9, 32),
-           (8, 40), (10, 40), (8, 52), (16, 32), (11, 52), (20, 32), (16, 52), (32, 32), (1, 160), (1, 400)]
+PLANNED = [(1, 1), (1, 8), (1, 32), (1, 40), (1, 52), (2, 20), (3, 20), (2, 52), (5, 20), (3, 40), (4, 32),
+           (16, 8), (17, 8), (7, 20), (3, 52), (4, 40), (9, 20), (6, 32), (4, 52), (12, 20), (8, 32),
+           (5, 52), (9, 32), (8, 40), (10, 40), (8, 52), (16, 32), (11, 52), (20, 32), (16, 52), (32, 32),
+           (1, 160), (1, 400)]
 
 
 @pytest.mark.parametrize("B,H", PLANNED)
