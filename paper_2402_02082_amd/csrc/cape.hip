@@ -46,19 +46,6 @@ __device__ __forceinline__ int key_id(uint64_t key) {
   return (int)(0xFFFFFFFFu - (uint32_t)key);
 }
 
-// Insert into a descending list of kTopK keys held in registers.
-__device__ __forceinline__ void insert_key(uint64_t (&top)[kTopK], uint64_t key) {
-  if (key <= top[kTopK - 1]) return;
-  top[kTopK - 1] = key;
-#pragma unroll
-  for (int j = kTopK - 1; j > 0; --j) {
-    const uint64_t hi = top[j - 1], lo = top[j];
-    const bool sw = lo > hi;
-    top[j - 1] = sw ? lo : hi;
-    top[j] = sw ? hi : lo;
-  }
-}
-
 // Top 8 of two descending lists of 8, descending (bitonic merge: the
 // element-wise max of a and reversed b holds the 8 largest keys as a bitonic
 // sequence, which three compare-exchange stages sort).
@@ -109,19 +96,23 @@ __device__ __forceinline__ float row16_max(float v) {
 }
 
 constexpr int kWaves = kThreads / 64;
-constexpr int kPerWave = 64;  // candidates a wave can hold
+constexpr int kPerWave = 128;  // candidates a wave can hold
 
 // Top-8 keys of one 4096-element part of one draft row.
 //
-// Bound: latency (one round of loads, then short dependent steps).  Keeping a
-// sorted top 8 per thread (16 insertions of up to seven 64-bit exchanges) and
-// merging the lists across lanes and waves took 9.8 us for 64 rows of 32000,
-// this takes 5.8 (5 rows: 7.5, now 4.6): a threshold leaves only a few candidates: every thread requests its
-// 16 values at once, the maxima of 16 thread groups are paired, and the
-// smallest of the eight pair maxima is passed by at least eight values and,
-// on values in random order, by about 22.  Those are ranked by counting.
-// Parts with more candidates in a wave than it can hold (many values equal to
-// the threshold, such as zeros) take the sorted lists.
+// Every thread requests its 16 values at once.  The maxima of 16 thread
+// groups are paired, and the smallest of the eight pair maxima is passed by
+// at least eight values and, on values in random order, by about 22.  Those
+// are ranked by counting.
+//
+// Where more values pass it than a wave can hold (many equal ones, as the
+// zeros of filtered rows, or sorted rows), the threshold is the largest of the
+// waves' eighth largest thread maxima: a wave's values above it are in at most
+// seven threads, and of those equal to it the first eight are enough.
+//
+// Bound: latency (one round of loads, then short dependent steps).  A sorted
+// top 8 per thread, merged across lanes and waves, took 9.8 us for 64 rows of
+// 32000 (5 rows: 7.5); this takes 5.8 (4.6).
 __global__ __launch_bounds__(kThreads) void cape_top8_part(const float* __restrict__ probs, int V,
                                                            uint64_t* __restrict__ top_out) {
   const int part = blockIdx.x, row = blockIdx.y, tid = threadIdx.x;
@@ -133,10 +124,12 @@ __global__ __launch_bounds__(kThreads) void cape_top8_part(const float* __restri
   __shared__ __attribute__((aligned(16))) float group_max[16];
   __shared__ uint64_t cand[kWaves][kPerWave];
   __shared__ int cand_n[kWaves];
+  __shared__ uint32_t wave_eighth[kWaves];
 
   // x[j]: the part's element index_of(j); elements past the row are -inf here
-  // and never candidates
-  const bool vec = (V & 3) == 0 && (((uintptr_t)p) & 15) == 0;
+  // and never candidates.  Float4 loads leave whole threads of a part below
+  // 4 * kThreads elements without any, and groups without a maximum.
+  const bool vec = (V & 3) == 0 && (((uintptr_t)p) & 15) == 0 && left >= 4 * kThreads;
   float x[16];
   if (vec) {
     const float4* p4 = (const float4*)(p + base);
@@ -172,63 +165,106 @@ __global__ __launch_bounds__(kThreads) void cape_top8_part(const float* __restri
 #pragma unroll
   for (int i = 0; i < 8; ++i) t = fminf(t, fmaxf(group_max[i], group_max[i + 8]));
 
+  const uint64_t below = (1ull << lane) - 1ull;
   int n = 0;
 #pragma unroll
   for (int j = 0; j < 16; ++j) {
     const bool hit = x[j] >= t && index_of(j) < left;
     const uint64_t hits = __ballot(hit);
     if (hits) {
-      const int slot = n + __popcll(hits & ((1ull << lane) - 1ull));
+      const int slot = n + __popcll(hits & below);
       if (hit && slot < kPerWave) cand[wave][slot] = rank_key(x[j], base + index_of(j));
       n += __popcll(hits);
     }
   }
-  if (lane == 0) cand_n[wave] = n;
-  __syncthreads();
-  int cn[kWaves], total = 0;
-  bool over = false;
-#pragma unroll
-  for (int w = 0; w < kWaves; ++w) {
-    cn[w] = __builtin_amdgcn_readfirstlane(cand_n[w]);
-    total += cn[w];
-    over |= cn[w] > kPerWave;
-  }
-  if (!over) {
-    // each wave ranks its own candidates against all (keys are distinct)
-    const uint64_t mine = lane < n ? cand[wave][lane] : 0;
-    int rank = 0;
+  int cn[kWaves], total;
+  auto meet = [&]() {  // every wave's candidates are in place; the largest count
+    if (lane == 0) cand_n[wave] = n;
+    __syncthreads();
+    int most = total = 0;
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) {
-#pragma unroll 4
-      for (int o = 0; o < cn[w]; ++o) rank += cand[w][o] > mine;
+      cn[w] = __builtin_amdgcn_readfirstlane(cand_n[w]);
+      total += cn[w];
+      most = max(most, cn[w]);
     }
-    if (lane < n && rank < kTopK) out[rank] = mine;
-    if (tid >= total && tid < kTopK) out[tid] = 0;  // a part of fewer than eight elements
-    return;
+    return most;
+  };
+  if (meet() > kPerWave) {
+    uint32_t o[16], top = 0;
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+      o[j] = index_of(j) < left ? ordered_bits(x[j]) : 0;
+      top = max(top, o[j]);
+    }
+    // the wave's eighth largest thread maximum: of the thread maxima that fewer
+    // than eight exceed, the one that most exceed
+    int above = 0;
+#pragma unroll
+    for (int i = 0; i < 64; ++i) above += (uint32_t)__builtin_amdgcn_readlane(top, i) > top;
+    uint64_t eighth = 0;
+#pragma unroll
+    for (int k = 0; k < kTopK; ++k) {
+      const uint64_t at = __ballot(above == k);
+      eighth = at ? at : eighth;
+    }
+    uint32_t e8 = __builtin_amdgcn_readlane(top, __ffsll((long long)eighth) - 1);
+    if (lane == 0) wave_eighth[wave] = e8;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) e8 = max(e8, wave_eighth[w]);
+    n = 0;
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+      const bool hit = o[j] > e8;
+      const uint64_t hits = __ballot(hit);
+      if (hit) cand[wave][n + __popcll(hits & below)] = rank_key(x[j], base + index_of(j));
+      n += __popcll(hits);
+    }
+    // equal values in the order of their ids: element by element of a thread
+    // where it holds four in a row, otherwise thread by thread
+    int ties = 0;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      if (ties < kTopK) {
+        bool tie[4];
+        int first[4], upto = ties;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          tie[e] = o[4 * u + e] == e8 && index_of(4 * u + e) < left;
+          const uint64_t hits = __ballot(tie[e]);
+          first[e] = __popcll(hits & below) + (vec ? 0 : upto);
+          upto += __popcll(hits);
+        }
+        int at = ties + first[0] + first[1] + first[2] + first[3];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int slot = vec ? at : first[e];
+          if (tie[e] && slot < kTopK) cand[wave][n + slot] = rank_key(x[4 * u + e], base + index_of(4 * u + e));
+          at += tie[e];
+        }
+        ties = upto;
+      }
+    }
+    n += min(ties, kTopK);
+    meet();
   }
 
-  uint64_t top[kTopK];
+  // each wave ranks its own candidates against all (keys are distinct)
 #pragma unroll
-  for (int j = 0; j < kTopK; ++j) top[j] = 0;  // below every real key
+  for (int own = lane; own < kPerWave; own += 64) {
+    if (own - lane < n) {
+      const uint64_t mine = own < n ? cand[wave][own] : 0;
+      int rank = 0;
 #pragma unroll
-  for (int j = 0; j < 16; ++j)
-    if (index_of(j) < left) insert_key(top, rank_key(x[j], base + index_of(j)));
-  // Merge the 64 lists of each wave with shuffles, then the 4 wave lists.
-  wave_merge_top8(top, 64);
-  __syncthreads();  // every wave has read cand
-  if (lane == 0) {
-#pragma unroll
-    for (int j = 0; j < kTopK; ++j) cand[wave][j] = top[j];
+      for (int w = 0; w < kWaves; ++w) {
+#pragma unroll 4
+        for (int i = 0; i < cn[w]; ++i) rank += cand[w][i] > mine;
+      }
+      if (own < n && rank < kTopK) out[rank] = mine;
+    }
   }
-  __syncthreads();
-  if (wave != 0) return;
-#pragma unroll
-  for (int j = 0; j < kTopK; ++j) top[j] = lane < kWaves ? cand[lane & (kWaves - 1)][j] : 0;
-  wave_merge_top8(top, kWaves);
-  if (lane == 0) {
-#pragma unroll
-    for (int j = 0; j < kTopK; ++j) out[j] = top[j];
-  }
+  if (tid >= total && tid < kTopK) out[tid] = 0;  // a part of fewer than eight elements
 }
 
 // S(p): 7, 5, 3, 1 on (0, 0.3], (0.3, 0.6], (0.6, 0.8], (0.8, 1].

@@ -210,6 +210,32 @@ def test_cape_candidate_threshold(V, rows):
     assert np.array_equal(nn.cpu().numpy(), w_n)
 
 
+def _expand(probs, n_max=24):
+    B = probs.shape[0]
+    tok = torch.full((B, n_max), -9, dtype=torch.int32, device="cuda")
+    par, nn = torch.full_like(tok, -9), torch.full((B,), -9, dtype=torch.int32, device="cuda")
+    glide.cape_expand(torch.from_numpy(probs).cuda(), 0, n_max, tok, par, nn)
+    torch.cuda.synchronize()
+    return [t.cpu().numpy() for t in (tok, par, nn)]
+
+
+@pytest.mark.parametrize("V", [100, 116, 1000, 1020, 1024, 1025, 2052, 4100, 5120, 12288])
+@pytest.mark.parametrize("kept", [0, 1, 4, 7, 8, 60])
+def test_cape_few_values_above_equal_ones(V, kept):
+    """More equal values than a wave holds candidates, with 0 to 60 larger ones
+    among them: the equal ones are taken in the order of their ids, whichever
+    threads and waves they are in."""
+    require_gpu()
+    rng = np.random.default_rng(1000 * kept + V)
+    probs = np.full((2, 6, V), 0.001, dtype=np.float32)
+    for row in probs.reshape(-1, V):
+        row[:rng.integers(0, V)] = 0.0          # the equal values begin anywhere
+        row[rng.choice(V, size=kept, replace=False)] = rng.uniform(0.002, 0.2, size=kept)
+    say("cape", dict(V=V, kept=kept))
+    for got, want in zip(_expand(probs), OC.cape_expand(probs, 0, 24)):
+        assert np.array_equal(got, want)
+
+
 @pytest.mark.parametrize("V", [1, 63, 4096, 32000, 32772, 50001])
 @pytest.mark.parametrize("rows", [20, 600])
 def test_argmax_masked_rows(V, rows):
