@@ -169,7 +169,7 @@ __global__ __launch_bounds__(kThreads) void cape_top8_part(const float* __restri
   int n = 0;
 #pragma unroll
   for (int j = 0; j < 16; ++j) {
-    const bool hit = x[j] >= t && index_of(j) < left;
+    const bool hit = !(x[j] < t) && index_of(j) < left;  // NaN: its key is the largest
     const uint64_t hits = __ballot(hit);
     if (hits) {
       const int slot = n + __popcll(hits & below);

@@ -236,6 +236,22 @@ def test_cape_few_values_above_equal_ones(V, kept):
         assert np.array_equal(got, want)
 
 
+@pytest.mark.parametrize("V", [100, 1024, 4100, 12288])
+@pytest.mark.parametrize("nans", [1, 9, 700, None])
+def test_cape_nan_rows_give_tokens(V, nans):
+    """NaN is outside the contract, but the outputs stay tokens: its key ranks
+    above every number's (ties by id), in rows of one to 700 NaN and of NaN
+    only."""
+    require_gpu()
+    rng = np.random.default_rng(V)
+    probs = rng.dirichlet(np.full(V, 0.3), size=(2, 3)).astype(np.float32)
+    for row in probs.reshape(-1, V):
+        row[rng.choice(V, size=min(nans or V, V), replace=False)] = np.nan
+    say("cape", dict(V=V, nans=nans))
+    for got, want in zip(_expand(probs), OC.cape_expand(np.where(np.isnan(probs), np.float32(2), probs), 0, 24)):
+        assert np.array_equal(got, want)
+
+
 @pytest.mark.parametrize("V", [1, 63, 4096, 32000, 32772, 50001])
 @pytest.mark.parametrize("rows", [20, 600])
 def test_argmax_masked_rows(V, rows):
