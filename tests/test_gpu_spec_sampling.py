@@ -124,3 +124,40 @@ def test_certain_rows(V):
     want_acc, want_tok = S.spec_sample_verify(tokens, pd, pt, u)
     assert np.array_equal(acc.cpu().numpy(), want_acc) and (want_acc == 0).all()
     assert np.array_equal(tok.cpu().numpy(), want_tok)
+
+
+@pytest.mark.parametrize("V", [32772, 40000, 65537, 70004, 140001])
+def test_regions_of_several_groups(V):
+    """Vocabularies past 32768, where a wave's region is more than the 2048
+    tokens it holds at once: the drawn token in the first, a middle and the
+    last group of the first, a middle and the last region, with half of the
+    mass on it and the rest spread over the row, after a rejection (residual)
+    and after an accepted chain (target row)."""
+    require_gpu()
+    say("spec_sample groups", V)
+    region = -(-V // 4096) * 256
+    at = sorted({min(V - 1, w * region + o) for w in (0, 7, 15) for o in (0, 2047, 2048, 4095, 4096, region - 1)})
+    B, gamma = 2 * len(at), 1
+    rng = np.random.default_rng(V)
+    base = rng.random(V).astype(np.float32)
+    base *= np.float32(0.5 / base.sum(dtype=np.float64))
+    pd, pt = np.zeros((B, gamma, V), dtype=np.float32), np.empty((B, gamma + 1, V), dtype=np.float32)
+    tokens, u = np.zeros((B, gamma), dtype=np.int32), np.zeros((B, gamma + 1), dtype=np.float32)
+    for b in range(B):
+        x, accepted = at[b // 2], b % 2
+        pt[b] = base
+        pt[b, :, x] += 0.5
+        tokens[b, 0] = (x + 5) % V
+        pd[b, 0, tokens[b, 0]] = base[tokens[b, 0]] if accepted else 1.0
+        u[b, 0] = 0.5
+        cdf = np.cumsum(pt[b, 1], dtype=np.float64)
+        u[b, 1] = (cdf[x] - 0.25) / cdf[-1]
+    dev = torch.device("cuda")
+    acc = torch.full((B,), -7, dtype=torch.int32, device=dev)
+    tok = torch.full((B,), -7, dtype=torch.int32, device=dev)
+    glide.spec_sample_verify(torch.from_numpy(tokens).to(dev), torch.from_numpy(pd).to(dev),
+                             torch.from_numpy(pt).to(dev), torch.from_numpy(u).to(dev), acc, tok)
+    torch.cuda.synchronize()
+    want_acc, want_tok = S.spec_sample_verify(tokens, pd, pt, u)
+    assert np.array_equal(acc.cpu().numpy(), want_acc) and want_acc.tolist() == [0, 1] * len(at)
+    assert np.array_equal(tok.cpu().numpy(), want_tok) and set(want_tok) == set(at)
