@@ -103,6 +103,14 @@ bool kept_workspace(const at::Tensor& on, PyObject* handle, size_t need, at::Ten
   return true;
 }
 
+// A reference that is given back with the scope.
+struct Held {
+  PyObject* o;
+  explicit Held(PyObject* owned) : o(owned) {}
+  Held(const Held&) = delete;
+  ~Held() { Py_XDECREF(o); }
+};
+
 void* ptr(const at::Tensor* t) { return t ? t->data_ptr() : nullptr; }
 
 // Runs `f` without the GIL (the call may wait for the device when it
@@ -181,15 +189,19 @@ PyObject* verify_commit(PyObject* const* a, Py_ssize_t n) {
     if (i == 2 ? !is_shape(*io[i], {B, N + 1}) : (i == 6 ? !is_shape(*io[i], {B, N}) : !is_shape(*io[i], {B})))
       return nullptr;
   }
-  const Py_ssize_t layers = PyList_GET_SIZE(a[3]);
-  if (layers != PyList_GET_SIZE(a[4]) || layers > 128) return nullptr;
+  // the caches themselves are held, not the lists: another thread may change
+  // those while the call runs without the GIL
+  const Held caches[2] = {Held(PyList_AsTuple(a[3])), Held(PyList_AsTuple(a[4]))};
+  if (!caches[0].o || !caches[1].o) return nullptr;
+  const Py_ssize_t layers = PyTuple_GET_SIZE(caches[0].o);
+  if (layers != PyTuple_GET_SIZE(caches[1].o) || layers > 128) return nullptr;
   int64_t H = 1, cap = N, D = GLIDE_HEAD_DIM;
   int dtype = GLIDE_BF16;
   void* p[2][128];
   const at::Tensor* ref = nullptr;
   for (int m = 0; m < 2; ++m)
     for (Py_ssize_t i = 0; i < layers; ++i) {
-      PyObject* o = PyList_GET_ITEM(a[3 + m], i);
+      PyObject* o = PyTuple_GET_ITEM(caches[m].o, i);
       if (!ref) {
         const at::Tensor* t = tensor(o);
         if (!t || (t->scalar_type() != kBf16 && t->scalar_type() != kF32)) return nullptr;

@@ -3,6 +3,9 @@ checks they stand in front of: plain calls give the same results on either
 path (an explicit stream takes the Python path), and every argument that the
 Python checks refuse is declined natively, so that the reason is raised."""
 
+import ctypes
+import weakref
+
 import pytest
 import torch
 
@@ -99,3 +102,32 @@ def test_native_declines_what_python_refuses(name):
             if name == "attn" and i == 4 or not (isinstance(x, torch.Tensor) and x.shape == a.shape
                                                  and x.dtype == a.dtype and x.is_cuda and x.is_contiguous()):
                 refused(args[:i] + [x] + args[i + 1:])
+
+
+def test_caches_outlive_their_lists_during_the_call():
+    """The commit's cache tensors stay alive until the C call returns, also when
+    the lists they were passed in are emptied meanwhile (as another thread
+    could: the call runs without the GIL).  The C call is a stand-in that
+    empties them and launches nothing."""
+    require_gpu()
+    args = _calls()["commit"][2]
+    caches = [weakref.ref(t) for t in args[3] + args[4]]
+    alive = []
+
+    @ctypes.CFUNCTYPE(ctypes.c_int, *glide.load().glide_verify_commit.argtypes)
+    def stand_in(*_):
+        args[3].clear()
+        args[4].clear()
+        alive.extend(c() is not None for c in caches)
+        return 0
+
+    nat = _lib._bind()
+    try:
+        nat.bind((0, 0, ctypes.cast(stand_in, ctypes.c_void_p).value, 0, 0, 0, 0, 0), _lib._raw_stream,
+                 _lib._ws_cache)
+        glide.glide_verify_commit(*args)
+    finally:
+        _lib._native = None
+        _lib._bind()
+    assert alive == [True] * 4
+    assert [c() for c in caches] == [None] * 4
