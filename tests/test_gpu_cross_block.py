@@ -139,10 +139,14 @@ def test_rows_matmul_packed(M, K, N, out_dtype):
 @pytest.mark.parametrize("M,K,N", [(129, 8, 1), (129, 64, 64), (191, 56, 130), (192, 72, 65), (257, 520, 100),
                                    (513, 136, 4097), (640, 4104, 4096), (2049, 72, 4100), (2048, 200, 4099)])
 def test_rows_matmul_tiles(M, K, N):
-    """More than 128 rows with a bf16 output: 2-D output tiles of every launch
-    shape (64 x 64, 128 x 64 and 256 x 128), with ragged last tiles, K below,
-    at and past a 64-wide chunk, and N that does and does not allow 8-byte
-    stores; the packed copy gives the same bits."""
+    """More than 128 rows with a bf16 output: 2-D output tiles of 64 x 64 and
+    128 x 64 (the last two cases), with ragged last tiles, K below, at and past
+    a 64-wide chunk, and N that does and does not allow 8-byte stores; the
+    packed copy gives the same bits."""
+    _check_tiles(M, K, N)
+
+
+def _check_tiles(M, K, N):
     require_gpu()
     say("rows_matmul tiles", dict(M=M, K=K, N=N))
     a = _bf16((M, K), 21 + M).cuda()
@@ -156,6 +160,31 @@ def test_rows_matmul_tiles(M, K, N):
     assert bool(torch.isnan(guard[M]).all())
     excess = bf16_ok(to64(got), OX.rows_matmul(to64(a), to64(w_t)))
     assert excess <= 0, excess
+
+
+def _tile_of(M, N):
+    """The output tile the launch takes: the least time per 64-wide K chunk with
+    its tiles dealt over 256 CUs (csrc/tile_matmul.hip)."""
+    def rounds(tm, tn):
+        return -(-(-(-M // tm) * -(-N // tn)) // 256)
+
+    big, mid, small = rounds(256, 128), 0.05 + 0.33 * rounds(128, 64), 0.06 + 0.19 * rounds(64, 64)
+    if big <= mid and big <= small:
+        return "256x128"
+    return "128x64" if mid <= small else "64x64"
+
+
+@pytest.mark.parametrize("tile,M,K,N", [
+    ("256x128", 2047, 200, 4095), ("256x128", 1793, 72, 4092), ("256x128", 2048, 56, 4096),
+    ("256x128", 2048, 64, 4096), ("256x128", 2048, 128, 4090), ("256x128", 1800, 1032, 4096),
+    ("256x128", 2048, 4096, 4096), ("256x128", 4000, 136, 2041), ("128x64", 1000, 4096, 2041),
+    ("128x64", 1025, 328, 1790), ("64x64", 300, 1096, 1500), ("64x64", 129, 4096, 8200)])
+def test_rows_matmul_tile_shapes(tile, M, K, N):
+    """Each tile shape, and for 256 x 128 -- eight waves on a two-deep ring --
+    ragged rows and columns, 8-byte and single stores, and K of less than a
+    chunk, of whole chunks, with a tail, and long."""
+    assert _tile_of(M, N) == tile
+    _check_tiles(M, K, N)
 
 
 def test_pack_layout():
