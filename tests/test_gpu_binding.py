@@ -104,6 +104,45 @@ def test_native_declines_what_python_refuses(name):
                 refused(args[:i] + [x] + args[i + 1:])
 
 
+@pytest.mark.parametrize("dtype", [BF, F32], ids=["bf16", "f32"])
+def test_commit_moves_the_same_rows_on_either_path(dtype):
+    """The commit of a path that skips nodes, so that rows move in every layer's
+    K and V (three layers, five heads, other lengths in each sequence): every
+    output and cache is the same on either path, and the rows are the accepted
+    nodes' own."""
+    require_gpu()
+    torch.manual_seed(4)
+    layers, heads, cap, path = 3, 5, 37, [1, 3, 5]
+    parents = torch.tensor([[-1, -1, 0, 1, 1, 3]] * B, dtype=I32, device="cuda")
+    tokens = torch.arange(10, 10 + B * N, dtype=I32, device="cuda").view(B, N)
+    logits = _rand((B, N + 1, V), F32)
+    for b in range(B):
+        for n in path:
+            logits[b, int(parents[b, n]) + 1, int(tokens[b, n])] = 50.0
+    lens = torch.tensor([30, 11], dtype=I32, device="cuda")
+    start = [[_rand((B, heads, cap, 128), dtype) for _ in range(layers)] for _ in range(2)]
+    results = []
+    for explicit in (False, True):   # an explicit stream takes the Python path
+        caches = [[t.clone() for t in ts] for ts in start]
+        outs = [_ints((B,)), _ints((B, N + 1)), _ints((B,)), _ints((B,)), _ints((B,)), _ints((B, N))]
+        args = [logits, tokens, parents, *caches, lens, *outs]
+        if explicit:
+            glide.glide_verify_commit(*args, stream=torch.cuda.current_stream())
+        else:
+            assert _lib._bind().verify_commit(*args, None) == 0
+        torch.cuda.synchronize()
+        results.append(outs + caches[0] + caches[1])
+    for x, y in zip(*results):
+        assert torch.equal(x, y)
+    assert results[0][2].tolist() == [3] * B and results[0][5][:, :3].tolist() == [path] * B
+    for before, after in zip(start[0] + start[1], results[0][6:]):
+        for b in range(B):
+            L0 = int(lens[b])
+            want = before[b].clone()
+            want[:, L0:L0 + 3] = before[b][:, [L0 + n for n in path]]
+            assert torch.equal(after[b], want)
+
+
 def test_caches_outlive_their_lists_during_the_call():
     """The commit's cache tensors stay alive until the C call returns, also when
     the lists they were passed in are emptied meanwhile (as another thread
