@@ -384,27 +384,24 @@ hipError_t launch_pack_rows_weights(const void* w_t, void* packed, int K, int N,
 
 hipError_t launch_rows_matmul(const void* a, const void* w, void* out, int M, int K, int N,
                               bool out_bf16, bool packed, hipStream_t stream) {
-  // More rows than one launch takes: 2-D output tiles for bf16 outputs (130
-  // rows of K = N = 4096: 30 -> 16 us, 2048 rows 337 -> 66 us).  They add a
-  // row's K steps in one chain, where the few-row kernels add four chains a
-  // quarter as long; next to a bf16 output's rounding that is nothing (both
-  // 1.66e-3 off float64), but a float32 output would lose half a digit, so
-  // it keeps the few-row kernels, each launch streaming the weights again.
-  if (M > kMaxMatmulRows && out_bf16) return launch_tile_matmul(a, w, out, M, K, N, packed, stream);
+  const uint16_t *ap = (const uint16_t*)a, *wp = (const uint16_t*)w;
+  if (out_bf16) {
+    // More rows than one launch takes: 2-D output tiles (130 rows of K = N =
+    // 4096: 30 -> 16 us, 2048 rows 335 -> 62 us).  They add a row's K steps in
+    // one chain, where the few-row kernels add four chains a quarter as long;
+    // next to a bf16 output's rounding that is nothing (both 1.66e-3 off
+    // float64), but a float32 output would lose half a digit, so it keeps the
+    // few-row kernels, each launch streaming the weights again.
+    if (M > kMaxMatmulRows) return launch_tile_matmul(a, w, out, M, K, N, packed, stream);
+    return packed ? launch_rows<uint16_t, true>(ap, wp, (uint16_t*)out, M, K, N, stream)
+                  : launch_rows<uint16_t, false>(ap, wp, (uint16_t*)out, M, K, N, stream);
+  }
   for (int m0 = 0; m0 < M; m0 += kMaxMatmulRows) {
     const int rows = min(kMaxMatmulRows, M - m0);
-    const uint16_t* ap = (const uint16_t*)a + (size_t)m0 * K;
-    const uint16_t* wp = (const uint16_t*)w;
-    hipError_t e;
-    if (out_bf16) {
-      uint16_t* op = (uint16_t*)out + (size_t)m0 * N;
-      e = packed ? launch_rows<uint16_t, true>(ap, wp, op, rows, K, N, stream)
-                 : launch_rows<uint16_t, false>(ap, wp, op, rows, K, N, stream);
-    } else {
-      float* op = (float*)out + (size_t)m0 * N;
-      e = packed ? launch_rows<float, true>(ap, wp, op, rows, K, N, stream)
-                 : launch_rows<float, false>(ap, wp, op, rows, K, N, stream);
-    }
+    const uint16_t* am = ap + (size_t)m0 * K;
+    float* op = (float*)out + (size_t)m0 * N;
+    const hipError_t e = packed ? launch_rows<float, true>(am, wp, op, rows, K, N, stream)
+                                : launch_rows<float, false>(am, wp, op, rows, K, N, stream);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
