@@ -5,10 +5,13 @@ given, takes their device pointers and calls the C entry point of the same
 name.  No computation happens in Python and there is no fallback: if the
 library is missing or a call fails, an exception is raised.
 
-The calls of the decoding loop try the native checks first (_native,
+glide_tree_attn, glide_verify_commit, cape_expand, spec_sample_verify,
+glide_rows_matmul and glide_block_attn try the native checks first (_native,
 csrc/binding.cpp: the same checks and the same call); where those decline --
 an explicit stream, a tensor subclass, or anything that fails a check -- the
-Python checks below them decide (ctypes), and raise with the reason.
+Python checks below them decide (ctypes), and raise with the reason.  The
+other calls, the packed projections and the cross block among them, are
+checked in Python alone.
 """
 
 import ctypes

@@ -1,5 +1,6 @@
-// The Python binding's fast path: argument checks and pointer marshalling of
-// the decoding loop's calls in native code.
+// The Python binding's fast path: argument checks and pointer marshalling in
+// native code, for the calls of the decoding loop and of draft training named
+// in Calls below.
 //
 // A decoding step makes tens of these calls of about ten microseconds of GPU
 // work each, and one checked and marshalled in Python took longer than that

@@ -16,9 +16,9 @@
 // would need 75 % of the product's time, where 128 x 128 tiles need all of
 // it.  The chunk loop must stay free of address arithmetic: with offsets
 // recomputed per load it issued four vector instructions per product and
-// took 75-82 us where it now takes 66.  K = N = 4096, row-major weights:
-// 2048 rows 337 -> 66 us (1040 TFLOP/s), 512 rows 87 -> 24 us, 130 rows
-// 30 -> 16 us against the few-row kernels.
+// took 75-82 us, without 62.  K = N = 4096, row-major weights: 2048 rows
+// 335 -> 62 us (1100 TFLOP/s), 512 rows 87 -> 24 us, 130 rows 30 -> 16 us
+// against the few-row kernels.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 

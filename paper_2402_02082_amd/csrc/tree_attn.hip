@@ -1,6 +1,6 @@
 // Split-K flash-decode attention of up to 64 query rows per (sequence, head)
 // against a KV cache, for gfx950; and the block-masked cross attention of
-// draft training, built from the same step.
+// draft training, on the same LDS ring with a step of its own (block_step).
 //
 // Computes hd = SoftMax(Q K^T * scale) V per head (arXiv 2402.02082, Sec. 4.1,
 // MultiHead / hd_j equations).  In tree mode a query row (tree node n) sees
@@ -696,7 +696,7 @@ __device__ __forceinline__ void merge_partials(const AttnArgs& a, int b, int h, 
 // rows behind the first round of CUs are then taken shortest first, so that
 // the longest sequences share with the shortest instead of with the middle
 // ones: 16 sequences x 32 heads of 1024..4096 keys, 5 rows 125 -> 110 us, of
-// 16K..32K keys 1040 -> 961 us, float32 (16 rows) 249 -> 218 us.  Past 512
+// 16K..32K keys 997 -> 918 us, float32 (16 rows) 249 -> 218 us.  Past 512
 // workgroups the order is longest first throughout (1024 of them: 224 us
 // against 240).
 __device__ __forceinline__ int seq_of_row(const int32_t* seq_lens, int B, int H, int splits, int paired, int y,
@@ -1284,8 +1284,9 @@ __device__ __forceinline__ void block_scores(const u32x4_t (&k)[2][4], const Bf1
 // vector work is cut down against the shared step:
 //  * the V^T operands come transposed out of LDS, which saves the 32 byte
 //    permutes of a step (about a quarter of its vector instructions; four
-//    sequences of 2048 positions, 32 heads, blocks of 5: 158.4 -> 149.5 us,
-//    870 -> 920 TFLOP/s);
+//    sequences of 2048 positions, 32 heads, blocks of 5: 158.4 -> 149.5 us
+//    a call under sustained load, 870 -> 920 TFLOP/s; a caller's separate
+//    calls on changing inputs 165 -> 156 us);
 //  * masking runs only in the steps that reach tile 0's limit (the
 //    smallest, wave-uniform); each lane then masks against its own limit;
 //  * the reference max moves only when some lane's scaled score passes it by
